@@ -1,0 +1,431 @@
+"""The measured calls of Token Radius Attention: what a video diffusion step asks
+of this package, from the smallest grids to the 720p layer.
+
+A model runs the path once per layer and denoising step.  On a warm-up
+(refresh) step it takes the dense output and the entropies, then budgets, radii
+and the block mask; on every other step it takes the sparse call with the lists
+it kept.  Each rank of a head-parallel model holds an eighth of the heads.  The
+cases below are those calls, each through its own entry point, and the whole
+chain on two small grids:
+
+    path     entropy with output -> budget/radius -> mask -> sparse call
+    refresh  entropy with the dense output          entropy  entropy only
+    dense    dense attention                        sparse   block-sparse call
+    token    token-level call                       radius   budget and radius
+    mask     block mask, lists and row order
+
+Inputs follow the package's synthetic workloads: features that are smooth over
+the grid, a per-query scale that spreads the attention temperature, Gaussian
+noise.  A sparse or token-level call's lists come from radii that follow the
+same scales (the entropy of Gaussian scores, the budget Eq. 8, the area of Eq.
+12 corrected for the frame's edges), lowered by one constant until the lists
+hold the case's share of the block pairs; a row keeps a block where the radius
+that a third of its queries reach covers the block's centre.
+"""
+import math
+
+import torch
+
+import paper_2608_02504_amd as tra
+
+TAU = 0.9
+FULL = tra.TRA_RADIUS_FULL
+
+
+def _case(name, op, dtype, heads, frames, height, width, **kw):
+    c = dict(name=name, op=op, dtype=dtype, heads=heads, frames=frames, height=height, width=width,
+             head_dim=128, block=128, text=0, density=1.0, gamma=0.6, s_min=0.25, s_max=4.0,
+             lse=False, layout="packed", rule="vote", budget="uniform", distance="2d")
+    c.update(kw)
+    return c
+
+
+def listed():
+    return [
+        # the smallest whole chain: the package's tiny fp32 grid, 256 tokens (launches and latency)
+        _case("path_tiny_fp32", "path", "fp32", 2, 4, 8, 8, head_dim=64, block=64),
+        # the whole chain on a small ragged bf16 grid (a preview-sized latent, 957 tokens)
+        _case("path_small_bf16", "path", "bf16", 2, 3, 11, 29),
+        # an fp32 warm-up call (checking a model in full precision at reduced resolution)
+        _case("refresh_fp32", "refresh", "fp32", 4, 9, 15, 26),
+        # the warm-up step's call of a 480p layer (Wan 1.3B: 12 heads, 32,760 tokens)
+        _case("refresh_480p", "refresh", "bf16", 12, 21, 30, 52),
+        # the steady sparse step of the 480p layer at 15 % of the block pairs
+        _case("sparse_480p", "sparse", "bf16", 12, 21, 30, 52, density=0.15),
+        # the same lists with the token mask inside the blocks
+        _case("token_480p", "token", "bf16", 12, 21, 30, 52, density=0.15),
+        # dense joint text-video attention, one rank's heads of eight (HunyuanVideo 720p, 256 text tokens)
+        _case("dense_joint_720p", "dense", "bf16", 3, 33, 45, 80, text=256, gamma=0.95, s_min=0.1, s_max=8.0,
+              lse=True),
+        # its steady sparse step at the paper's lowest density, with the log-sum-exp
+        _case("sparse_joint_720p", "sparse", "bf16", 3, 33, 45, 80, text=256, gamma=0.95, s_min=0.1, s_max=8.0,
+              density=0.09, lse=True),
+        # entropies alone, one rank's heads of eight of the 720p layer (Wan 14B: 40 heads, 75,600 tokens)
+        _case("entropy_720p", "entropy", "bf16", 5, 21, 45, 80),
+        # budgets and radii of the whole 720p layer
+        _case("radius_720p", "radius", "bf16", 40, 21, 45, 80, density=0.15),
+        # its block mask, lists and row order
+        _case("mask_720p", "mask", "bf16", 40, 21, 45, 80, density=0.15),
+        # the headline: its steady sparse step at 15 % of the block pairs
+        _case("sparse_720p", "sparse", "bf16", 40, 21, 45, 80, density=0.15),
+    ]
+
+
+def draw(rng):
+    """One more case: the listed calls on other grids, head counts and options."""
+    def log_int(lo, hi):
+        return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+    while True:
+        op = rng.choice(["path", "refresh", "refresh", "dense", "sparse", "sparse", "sparse", "token", "entropy",
+                         "radius", "mask"])
+        dtype = "fp32" if op in ("path", "refresh", "dense", "sparse") and rng.random() < 0.2 else "bf16"
+        d = 128 if rng.random() < 0.75 else 64
+        c = _case("", op, dtype, log_int(1, 40), log_int(2, 33), log_int(8, 45), log_int(8, 80), head_dim=d,
+                  block=64 if dtype == "fp32" and rng.random() < 0.5 else 128)
+        del c["name"]
+        if rng.random() < 0.3:
+            c["text"] = log_int(1, 300)
+        if rng.random() < 0.3:
+            c.update(gamma=0.95, s_min=0.1, s_max=8.0)
+        c["density"] = round(math.exp(rng.uniform(math.log(0.08), math.log(0.4))), 3)
+        c["lse"] = op in ("dense", "sparse", "token") and rng.random() < 0.5
+        if op in ("sparse", "token", "mask") and rng.random() < 0.2 and c["block"] == 128:
+            c["layout"] = "tiles"
+        if op == "mask":
+            c["rule"] = rng.choice(["vote", "vote", "union"])
+            c["distance"] = rng.choice(["2d", "2d", "1d"])
+        if op == "radius":
+            c["budget"] = rng.choice(["uniform", "lognormal"])
+        S = _tokens(c)
+        if S < 128 or c["height"] * c["width"] < 128 and op == "token":
+            continue
+        pairs = c["heads"] * S * S * (c["density"] if op in ("sparse", "token") else 1.0)
+        most = 4 * 3510 ** 2 if dtype == "fp32" else {"path": 1e9, "radius": 40 * 75600.0 ** 2, "mask": 40 * 75600.0 ** 2,
+                                                      "token": 8e9, "sparse": 3e10}.get(op, 2.5e10)
+        if pairs <= most:
+            return c
+
+
+# ------------------------------------------------------------------ shapes
+def _tokens(c):
+    return c["frames"] * c["height"] * c["width"] + c["text"]
+
+
+def _tiles(c):
+    return (8, 8) if c["block"] == 64 else (8, 16)
+
+
+def _blocks(c):
+    """Blocks per head of the block layout."""
+    th, tw = _tiles(c)
+    if c["layout"] == "tiles":
+        return c["frames"] * -(-c["height"] // th) * -(-c["width"] // tw) + -(-c["text"] // c["block"])
+    return -(-_tokens(c) // c["block"])
+
+
+def _plan(c):
+    th, tw = _tiles(c)
+    return tra.Plan(tra.Config(1, c["heads"], c["frames"], c["height"], c["width"], c["head_dim"], block=c["block"],
+                               tile_h=th, tile_w=tw, dtype=c["dtype"], rule=c["rule"], tau=TAU, gamma=c["gamma"],
+                               budget=c["budget"], distance=c["distance"], text_tokens=c["text"],
+                               block_layout=c["layout"]))
+
+
+def _order(c):
+    """Token index of every position of the block layout (tile-major, text last), -1 at padding; [NB, block]."""
+    F, H, W, b = c["frames"], c["height"], c["width"], c["block"]
+    th, tw = _tiles(c)
+    x = torch.arange(H).repeat_interleave(W)
+    y = torch.arange(W).repeat(H)
+    tile = (x // th) * (-(-W // tw)) + y // tw
+    raster = torch.arange(H * W)
+    frame = torch.argsort(tile * (H * W) + raster)  # tiles in order, row-major inside a tile
+    n_text = c["text"]
+    if c["layout"] == "tiles":
+        n_tiles = -(-H // th) * (-(-W // tw))
+        one = torch.full((n_tiles, b), -1)
+        first = torch.searchsorted(tile[frame], torch.arange(n_tiles))
+        one[tile[frame], torch.arange(H * W) - first[tile[frame]]] = frame
+        parts = [torch.where(one >= 0, one + f * H * W, one) for f in range(F)]
+        if n_text:
+            text = torch.full((-(-n_text // b) * b,), -1)
+            text[:n_text] = F * H * W + torch.arange(n_text)
+            parts.append(text.view(-1, b))
+        return torch.cat(parts).cuda()
+    p = (frame[None, :] + (torch.arange(F) * H * W)[:, None]).reshape(-1)
+    p = torch.cat([p, F * H * W + torch.arange(n_text)])
+    p = torch.cat([p, torch.full((-len(p) % b,), -1)])
+    return p.view(-1, b).cuda()
+
+
+# ------------------------------------------------------------------ inputs
+def _qkv(c, g):
+    """q, k, v [1, heads, S, d] and the per-query scales [heads, S]."""
+    F, H, W, T, n, d = c["frames"], c["height"], c["width"], c["text"], c["heads"], c["head_dim"]
+    S = _tokens(c)
+    dt = torch.bfloat16 if c["dtype"] == "bf16" else torch.float32
+
+    def normal(*shape):
+        return torch.randn(*shape, generator=g, device="cuda")
+
+    i = torch.arange(F * H * W, device="cuda")
+    pos = torch.stack([(i // (H * W) + 0.5) / F, (i // W % H + 0.5) / H, (i % W + 0.5) / W], 1)
+    feats = math.sqrt(2.0) * torch.cos(2 * math.pi * (pos @ (2.0 * normal(3, 64)) + torch.rand(64, generator=g, device="cuda")))
+    feats = torch.cat([feats, normal(T, 64)])
+    s = torch.exp(torch.empty(n, S, device="cuda").uniform_(math.log(c["s_min"]), math.log(c["s_max"]), generator=g))
+    q, k, v = (torch.empty(1, n, S, d, dtype=dt, device="cuda") for _ in range(3))
+    for h in range(n):
+        q[0, h] = s[h, :, None] * (feats @ (0.125 * normal(64, d)) + 0.5 * normal(S, d))
+        k[0, h] = feats @ (0.125 * normal(64, d)) + 0.5 * normal(S, d)
+        v[0, h] = normal(S, d)
+    return q, k, v, s
+
+
+def _entropy(c, s, g):
+    """Entropies (nats) that Gaussian scores of these scales have over S keys."""
+    h = math.log(_tokens(c)) - 0.78125 * s.double() ** 2
+    return torch.clamp(h + 0.05 * torch.randn(s.shape, generator=g, device="cuda").double(), min=0.01)
+
+
+def _radii(c, entropy):
+    """Squared radii [heads, S] of the entropies: budget over the area that a unit squared radius covers."""
+    hw, n_cap = c["height"] * c["width"], (c["height"] - 1) ** 2 + (c["width"] - 1) ** 2
+    area = math.pi * sum((1 if f == 0 else 2) * math.exp(-2 * c["gamma"] * f) for f in range(c["frames"]))
+    budget = TAU * torch.exp(entropy)
+    n = torch.floor(budget / area * torch.exp(budget / (4.6 * hw)).clamp(max=1e6))
+    n = torch.where(n > n_cap, float(FULL), n)
+    n[:, c["frames"] * hw:] = FULL
+    return n
+
+
+def _keep(c, order, n):
+    """Block mask [heads, NB, NB] of squared radii n [heads, S]."""
+    H, W = c["height"], c["width"]
+    n_video = c["frames"] * H * W
+    valid = (order >= 0) & (order < n_video)
+    size = valid.sum(1)
+    text = ((order >= n_video).sum(1) > 0)
+    i = order.clamp(min=0)
+    mean = lambda t: (t * valid).sum(1) / size.clamp(min=1)
+    f, x, y = (mean(t.double()) for t in (i // (H * W), i // W % H, i % W))
+    per_query = torch.where(valid, n[:, i], -1.0)
+    top = torch.sort(per_query, dim=2, descending=True).values  # [heads, NB, block]
+    third = top.gather(2, (size // 3).clamp(max=order.shape[1] - 1)[None, :, None].expand(n.shape[0], -1, 1))
+    dist = (x[:, None] - x) ** 2 + (y[:, None] - y) ** 2
+    reach = torch.exp(-2 * c["gamma"] * (f[:, None] - f).abs())
+    keep = dist <= third * reach
+    return keep | (third >= FULL) | torch.eye(len(f), dtype=torch.bool, device="cuda") | text[:, None] | text
+
+
+def _lists(c, s, g):
+    """Radii, row lengths and block lists at the case's density, and the entropies behind them."""
+    order, h = _order(c), _entropy(c, s, g)
+    lo, hi = 0.0, math.log(_tokens(c)) + 1.0
+    for _ in range(14):
+        mid = 0.5 * (lo + hi)
+        if float(_keep(c, order, _radii(c, h - mid)).double().mean()) > c["density"]:
+            lo = mid
+        else:
+            hi = mid
+    n = _radii(c, h - hi)
+    keep = _keep(c, order, n)
+    nb = keep.shape[1]
+    ids = torch.where(keep, torch.arange(nb, device="cuda"), nb)
+    cols = torch.sort(ids, dim=2).values
+    cols = torch.where(cols == nb, -1, cols).int()[None].contiguous()
+    return n.int()[None].contiguous(), keep.sum(2).int()[None].contiguous(), cols, (h - hi).float()[None].contiguous()
+
+
+def _inputs(case, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed * 2 + 1)
+    st = {}
+    if case["op"] in ("radius", "mask"):
+        s = torch.exp(torch.empty(case["heads"], _tokens(case), device="cuda")
+                      .uniform_(math.log(case["s_min"]), math.log(case["s_max"]), generator=g))
+    else:
+        st["q"], st["k"], st["v"], s = _qkv(case, g)
+    if case["op"] in ("sparse", "token", "radius", "mask"):
+        st["radius"], st["cnt"], st["cols"], st["entropy_in"] = _lists(case, s, g)
+    return st
+
+
+def prepare(case, seed):
+    st = _inputs(case, seed)
+    op, heads, S = case["op"], case["heads"], _tokens(case)
+    plan = _plan(case)
+    nb = plan.n_blocks
+    st["op"], st["plan"] = op, plan
+    new = lambda dtype, *shape: torch.empty(1, heads, *shape, dtype=dtype, device="cuda")
+    if op in ("path", "refresh", "dense", "sparse", "token"):
+        st["o"] = torch.empty_like(st["q"])
+    if op in ("path", "refresh", "entropy"):
+        st["entropy"] = new(torch.float32, S)
+    st["lse"] = new(torch.float32, S) if case["lse"] else None
+    if op == "path":
+        st["o_sparse"] = torch.empty_like(st["q"])
+    if op in ("path", "radius"):
+        st["budget_out"], st["radius_out"] = new(torch.int32, S), new(torch.int32, S)
+    if op in ("path", "mask"):
+        st["cnt_out"], st["cols_out"] = new(torch.int32, nb), new(torch.int32, nb, nb)
+        st["order_out"] = torch.empty(heads * nb, dtype=torch.int32, device="cuda") if op == "mask" else None
+    return st
+
+
+def run(st):
+    op, plan = st["op"], st["plan"]
+    q, k, v = (st.get(n) for n in ("q", "k", "v"))
+    if op == "path":
+        tra.tra_entropy(plan, q, k, v, st["o"], st["entropy"])
+        tra.tra_budget_radius(plan, st["entropy"], st["budget_out"], st["radius_out"])
+        tra.tra_build_block_mask(plan, st["radius_out"], None, st["cnt_out"], st["cols_out"], None)
+        tra.tra_sparse_attention(plan, q, k, v, st["cnt_out"], st["cols_out"], None, st["o_sparse"], None)
+        return {n: st[n] for n in ("o", "entropy", "budget_out", "radius_out", "cnt_out", "cols_out", "o_sparse")}
+    if op == "refresh":
+        tra.tra_entropy(plan, q, k, v, st["o"], st["entropy"])
+        return {"o": st["o"], "entropy": st["entropy"]}
+    if op == "entropy":
+        tra.tra_entropy(plan, q, k, None, None, st["entropy"])
+        return {"entropy": st["entropy"]}
+    if op == "radius":
+        tra.tra_budget_radius(plan, st["entropy_in"], st["budget_out"], st["radius_out"])
+        return {"budget_out": st["budget_out"], "radius_out": st["radius_out"]}
+    if op == "mask":
+        tra.tra_build_block_mask(plan, st["radius"], None, st["cnt_out"], st["cols_out"], st["order_out"])
+        return {"cnt_out": st["cnt_out"], "cols_out": st["cols_out"], "order_out": st["order_out"]}
+    if op == "dense":
+        tra.tra_dense_attention(plan, q, k, v, st["o"], st["lse"])
+    elif op == "sparse":
+        tra.tra_sparse_attention(plan, q, k, v, st["cnt"], st["cols"], None, st["o"], st["lse"])
+    else:
+        tra.tra_token_attention(plan, q, k, v, st["radius"], st["cnt"], st["cols"], None, st["o"], st["lse"])
+    return {"o": st["o"]} if st["lse"] is None else {"o": st["o"], "lse": st["lse"]}
+
+
+# ------------------------------------------------------------------ work, tolerances, exact results
+def work(case):
+    op, heads, d, S = case["op"], case["heads"], case["head_dim"], _tokens(case)
+    size = 2 if case["dtype"] == "bf16" else 4
+    nb = _blocks(case)
+    tensor, per, pairs = heads * S * d * size, heads * S * 4, heads * S * S
+    lists = heads * nb * (nb + 1) * 4
+    if op == "radius":
+        return {"bytes": 3 * per, "flops": 0}
+    if op == "mask":
+        return {"bytes": per + lists + heads * nb * 4, "flops": 0}
+    if op == "entropy":
+        return {"bytes": 2 * tensor + per, "flops": 2 * d * pairs}
+    if op == "refresh":
+        return {"bytes": 4 * tensor + per, "flops": 4 * d * pairs}
+    if op == "dense":
+        return {"bytes": 4 * tensor + per * case["lse"], "flops": 4 * d * pairs}
+    if op == "path":  # with these scales the mask keeps nearly every block
+        return {"bytes": 5 * tensor + 3 * per + lists, "flops": 8 * d * pairs}
+    kept = case["density"] * (2 / 3 if op == "token" else 1.0)  # about two thirds of a kept pair's tokens are covered
+    return {"bytes": 4 * tensor + per * (case["lse"] + (op == "token")) + lists * case["density"],
+            "flops": int(4 * d * pairs * kept)}
+
+
+def tolerance(case):
+    if case["op"] in ("radius", "mask"):
+        return "exact"
+    if case["op"] == "entropy":
+        return {"rel": 1e-6, "max": 1e-4}
+    if case["dtype"] == "fp32":
+        return {"rel": 2e-5, "max": 1e-3, "differ": 0.01}
+    return {"rel": 1e-2, "max": 0.15, "differ": 0.01}
+
+
+def _exact_rows(q, k, v, alpha, out, ent, lse, rows):
+    """Softmax attention of query rows `rows` of one head over all of k, v in 64 bits."""
+    x = (q[rows] @ k.T) * alpha
+    m = x.max(1, keepdim=True).values
+    x -= m
+    p = torch.exp(x)
+    z = p.sum(1, keepdim=True)
+    if ent is not None:
+        ent[rows] = (torch.log(z) - (p * x).sum(1, keepdim=True) / z)[:, 0]
+    if lse is not None:
+        lse[rows] = (m + torch.log(z))[:, 0]
+    if out is not None:
+        out[rows] = (p @ v) / z
+
+
+def _exact_radius(case, st):
+    """Eqs. 8 / App. A.2, 13 and 14 in 64 bits, by the counts of every candidate radius at every pixel."""
+    F, H, W = case["frames"], case["height"], case["width"]
+    S, n_cap = _tokens(case), (H - 1) ** 2 + (W - 1) ** 2
+    h = st["entropy_in"][0].double()
+    if case["budget"] == "uniform":
+        k = torch.ceil(TAU * torch.exp(h))
+    else:
+        sigma = torch.sqrt(2 * (math.log(S) - h).clamp(min=0))
+        z = math.sqrt(2) * float(torch.erfinv(torch.tensor(2 * TAU - 1, dtype=torch.float64)))
+        k = torch.ceil(S * 0.5 * torch.erfc((sigma - z) / math.sqrt(2)))
+    k = k.clamp(1, S).long()
+    n = torch.full_like(k, FULL)
+    radii = torch.arange(n_cap + 1, device="cuda").double()
+    thr = [torch.floor(radii * math.exp(-2 * case["gamma"] * f)).long() for f in range(F)]
+    ys, xs = torch.meshgrid(torch.arange(H), torch.arange(W), indexing="ij")
+    heads = torch.arange(case["heads"], device="cuda")[:, None]
+    for x in range(H):
+        d2 = ((ys[None] - x) ** 2 + (xs[None] - torch.arange(W)[:, None, None]) ** 2).reshape(W, -1).cuda()
+        disk = torch.zeros(W, n_cap + 1, dtype=torch.long, device="cuda").scatter_add_(1, d2, torch.ones_like(d2)).cumsum(1)
+        by_frame = torch.stack([disk[:, t] for t in thr])  # [F, W, n_cap + 1]
+        for f in range(F):
+            count = sum(((f - e >= 0) + (e > 0 and f + e < F)) * by_frame[e] for e in range(F))
+            tok = (f * H + x) * W + torch.arange(W, device="cuda")
+            want = k[:, tok].T.contiguous()
+            at = torch.searchsorted(count, want)
+            n[heads, tok] = torch.where(at > n_cap, FULL, at).T
+    k[:, F * H * W:], n[:, F * H * W:] = S, FULL
+    return {"budget_out": k.int()[None], "radius_out": n.int()[None]}
+
+
+def exact(case, seed):
+    op, heads, S, d = case["op"], case["heads"], _tokens(case), case["head_dim"]
+    if op == "mask":  # whole numbers, compared as they are
+        return None
+    st = _inputs(case, seed)
+    if op == "radius":
+        return None if case["budget"] != "uniform" else _exact_radius(case, st)
+    alpha = 1.0 / math.sqrt(d)
+    with_o, with_ent = op != "entropy", op in ("path", "refresh", "entropy")
+    o = torch.empty(heads, S, d, dtype=torch.float64, device="cuda") if with_o else None
+    ent = torch.empty(heads, S, dtype=torch.float64, device="cuda") if with_ent else None
+    lse = torch.empty(heads, S, dtype=torch.float64, device="cuda") if case["lse"] else None
+    if op in ("sparse", "token"):
+        order = _order(case)
+        nv, H, W, F = case["frames"] * case["height"] * case["width"], case["height"], case["width"], case["frames"]
+        n_cap = (H - 1) ** 2 + (W - 1) ** 2
+        decay = torch.exp(-2 * case["gamma"] * torch.arange(F, device="cuda").double())
+        cnt = st["cnt"][0].tolist()
+        toks = [t[t >= 0] for t in order]
+    for h in range(heads):
+        q, k, v = (st[n][0, h].double() for n in ("q", "k", "v"))
+        oh, eh, lh = (t[h] if t is not None else None for t in (o, ent, lse))
+        if op not in ("sparse", "token"):
+            step = max(1, (1 << 28) // S)
+            for r in range(0, S, step):
+                _exact_rows(q, k, v, alpha, oh, eh, lh, slice(r, r + step))
+            continue
+        for u, rows in enumerate(toks):
+            keys = order[st["cols"][0, h, u, :cnt[h][u]].long()].reshape(-1)
+            if case["layout"] == "tiles" or case["text"] or S % case["block"]:
+                keys = keys[keys >= 0]
+            x = (q[rows] @ k[keys].T) * alpha
+            if op == "token":
+                n = st["radius"][0, h, rows].double()[:, None]
+                free = (n > n_cap) | (rows >= nv)[:, None] | (keys >= nv)
+                fi, fj = rows[:, None] // (H * W), keys // (H * W)
+                dist = (rows[:, None] // W % H - keys // W % H) ** 2 + (rows[:, None] % W - keys % W) ** 2
+                t = torch.floor(n * decay[(fi - fj).abs().clamp(max=F - 1)])
+                x.masked_fill_(~(free | (dist <= t)), -math.inf)
+            if lh is not None:
+                lh[rows] = torch.logsumexp(x, 1)
+            oh[rows] = torch.softmax(x, 1) @ v[keys]
+    out = {"o": o, "entropy": ent, "lse": lse}
+    out = {n: t[None] for n, t in out.items() if t is not None}
+    if op == "path":
+        out.update(budget_out=None, radius_out=None, cnt_out=None, cols_out=None, o_sparse=None)
+    return out
