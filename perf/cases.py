@@ -18,9 +18,10 @@ Inputs follow the package's synthetic workloads: features that are smooth over
 the grid, a per-query scale that spreads the attention temperature, Gaussian
 noise.  A sparse or token-level call's lists come from radii that follow the
 same scales (the entropy of Gaussian scores, the budget Eq. 8, the area of Eq.
-12 corrected for the frame's edges), lowered by one constant until the lists
-hold the case's share of the block pairs; a row keeps a block where the radius
-that a third of its queries reach covers the block's centre.
+12 corrected for the grid's edges), the entropies lowered by one constant until
+the lists hold the case's share of the block pairs; a row keeps a block where
+the radius that a third of its queries reach covers the block's centre.  Rows
+near the grid's ends, where the full radius comes sooner, keep every block.
 """
 import math
 
@@ -188,15 +189,27 @@ def _entropy(c, s, g):
     return torch.clamp(h + 0.05 * torch.randn(s.shape, generator=g, device="cuda").double(), min=0.01)
 
 
-def _radii(c, entropy):
-    """Squared radii [heads, S] of the entropies: budget over the area that a unit squared radius covers."""
-    hw, n_cap = c["height"] * c["width"], (c["height"] - 1) ** 2 + (c["width"] - 1) ** 2
-    area = math.pi * sum((1 if f == 0 else 2) * math.exp(-2 * c["gamma"] * f) for f in range(c["frames"]))
-    budget = TAU * torch.exp(entropy)
-    n = torch.floor(budget / area * torch.exp(budget / (4.6 * hw)).clamp(max=1e6))
-    n = torch.where(n > n_cap, float(FULL), n)
-    n[:, c["frames"] * hw:] = FULL
-    return n
+def _reach(c):
+    """Per video token: keys per unit squared radius away from the edges, and the most keys a radius below FULL covers."""
+    F, H, W = c["frames"], c["height"], c["width"]
+    n_cap = (H - 1) ** 2 + (W - 1) ** 2
+    i = torch.arange(H * W, device="cuda")
+    dist = (i[:, None] // W - i // W) ** 2 + (i[:, None] % W - i % W) ** 2
+    decay = [math.exp(-2 * c["gamma"] * f) for f in range(F)]
+    disk = torch.stack([(dist <= math.floor(n_cap * e)).sum(1) for e in decay]).double()  # [F, H * W]
+    apart = (torch.arange(F)[:, None] - torch.arange(F)).abs()
+    area = math.pi * torch.tensor(decay, dtype=torch.float64)[apart].sum(1)
+    return area.repeat_interleave(H * W).cuda(), disk[apart.cuda()].sum(1).reshape(-1)
+
+
+def _radii(c, entropy, area, most):
+    """Squared radii [heads, S] of the entropies: the budget over the area that a unit squared radius covers, more
+    where the disks leave the frame (the largest radius at the most keys any covers, FULL above)."""
+    n_cap, nv = (c["height"] - 1) ** 2 + (c["width"] - 1) ** 2, area.shape[0]
+    budget = TAU * torch.exp(entropy[:, :nv])
+    n = torch.floor(budget / area * torch.exp((budget / most).clamp(max=1.0) * torch.log(n_cap * area / most)))
+    n = torch.where(budget > most, float(FULL), n.clamp(max=n_cap))
+    return torch.cat([n, torch.full_like(entropy[:, nv:], FULL)], 1)
 
 
 def _keep(c, order, n):
@@ -220,15 +233,15 @@ def _keep(c, order, n):
 
 def _lists(c, s, g):
     """Radii, row lengths and block lists at the case's density, and the entropies behind them."""
-    order, h = _order(c), _entropy(c, s, g)
+    order, h, reach = _order(c), _entropy(c, s, g), _reach(c)
     lo, hi = 0.0, math.log(_tokens(c)) + 1.0
     for _ in range(14):
         mid = 0.5 * (lo + hi)
-        if float(_keep(c, order, _radii(c, h - mid)).double().mean()) > c["density"]:
+        if float(_keep(c, order, _radii(c, h - mid, *reach)).double().mean()) > c["density"]:
             lo = mid
         else:
             hi = mid
-    n = _radii(c, h - hi)
+    n = _radii(c, h - hi, *reach)
     keep = _keep(c, order, n)
     nb = keep.shape[1]
     ids = torch.where(keep, torch.arange(nb, device="cuda"), nb)
