@@ -75,8 +75,8 @@
  *     transposed in 64-key tiles), 2 x batch x heads x NB x 128 x head_dim x 2
  *     bytes, rewritten by every call, plus 512 bytes of row-queue counters
  *     that the call resets and draws its query-block rows from;
- *   tra_sparse_attention, in addition: the work-unit tables and the split
- *     rows' partial results, (head_dim + 3) x 512 bytes for each of up to
+ *   tra_sparse_attention and tra_token_attention, in addition: the work-unit
+ *     tables and the split rows' partial results, (head_dim + 3) x 512 bytes for each of up to
  *     32 G + 1 pieces (G the workgroups the GPU holds at once; 1.65 GB at
  *     head_dim 128 on MI355X, less where the plan has fewer blocks);
  *   tra_build_block_mask with a non-NULL order: the counting-sort histograms
@@ -339,7 +339,8 @@ tra_status tra_sparse_attention(tra_plan plan, const void* q, const void* k,
  * covers no listed key gets o = 0, lse = -inf.  Whole 128-key tiles that none
  * of a wave's 32 queries covers are skipped.  (bf16, 2-D: the test is
  * evaluated as an exact integer dot product of per-query and per-key vectors on
- * the matrix cores; the decisions are the same.)  bf16 plans need every threshold
+ * the matrix cores; the decisions are the same.)  Long lists are cut and merged as
+ * in tra_sparse_attention.  bf16 plans need every threshold
  * below 65536 (n_cap <= 65535 for 2-D, floor(pi/2 n_cap) <= 65535 for 1-D)
  * and, with the packed layout, at least one block of video tokens per frame
  * (H*W >= block), else TRA_ERR_UNSUPPORTED.  workspace: TRA_CALL_TOKEN. */

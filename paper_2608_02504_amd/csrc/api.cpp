@@ -95,7 +95,7 @@ WsLayout ws_layout(const tra_plan_s& p, int call) {
     L.kt = take(kv);
     L.vt = take(kv);
     L.ctr = take(tra::kRowCounters * sizeof(int32_t));
-    if (call == TRA_CALL_SPARSE) {
+    if (call == TRA_CALL_SPARSE || call == TRA_CALL_TOKEN) {
       L.units = take((size_t)p.units_cap * 4 * sizeof(int32_t));
       L.splits = take((size_t)p.splits_cap * 4 * sizeof(int32_t));
       L.hdr = take(tra::kUnitHdrInts * sizeof(int32_t));
@@ -130,7 +130,7 @@ tra_status bind_workspace(tra_plan p, int call, bool needed, void* ws, size_t ws
   out->d_kt = (uint16_t*)(b + L.kt);
   out->d_vt = (uint16_t*)(b + L.vt);
   out->d_row_ctr = (int32_t*)(b + L.ctr);
-  if (call == TRA_CALL_SPARSE) {
+  if (call == TRA_CALL_SPARSE || call == TRA_CALL_TOKEN) {
     out->d_units = (int32_t*)(b + L.units);
     out->d_splits = (int32_t*)(b + L.splits);
     out->d_unit_hdr = (int32_t*)(b + L.hdr);

@@ -25,8 +25,8 @@
 //   is persistent: as many workgroups as can be resident, each taking rows
 //   from a row queue (per-XCD contiguous ranges with stealing, see next_row)
 //   until it is drained.  Several workgroups share a CU, so a SIMD can run one
-//   workgroup's matrix phase while another is in its softmax.  Block-sparse
-//   calls take work units instead of rows: long rows are cut into pieces whose
+//   workgroup's matrix phase while another is in its softmax.  Block-sparse and
+//   token-level calls take work units instead of rows: long rows are cut into pieces whose
 //   partial results a merge kernel combines, and each XCD's segment of the
 //   unit table lists its split pieces first, piece-major, so that the
 //   workgroups of one XCD walk the same key range (see plan_units_kernel).
@@ -532,31 +532,42 @@ __device__ __forceinline__ void token_mask_mfma(f32x16 (&s)[4], const lds_u8* __
   }
 }
 
-// Row queue of the persistent attention kernels (thread 0 of a workgroup only).  Without a
-// caller order the rows are split into 8 contiguous ranges, one per XCD (the
+// Row queue of the dense, entropy and fused kernels (thread 0 of a workgroup
+// only).  The rows are split into 8 contiguous ranges, one per XCD (the
 // workgroup with index b runs on XCD b mod 8), each drained through its own
 // counter: the rows an XCD has in flight are neighbouring query blocks of one
 // head, which share most key tiles in its L2.  A workgroup whose range is
 // drained takes rows from the next ranges in turn, so an XCD that runs at a
-// higher clock ends up doing more rows.  With a caller order, one counter walks
-// it (entries outside [0, rows) are skipped).  Returns -1 once all is drained.
+// higher clock ends up doing more rows.  Returns -1 once all is drained.
 // ctr: kRowCounters ints, zero before the launch; counter x at ctr[16 x].
-__device__ __forceinline__ int next_row(int32_t* ctr, const int32_t* __restrict__ order, int rows, int xcd,
-                                            int& steal) {
-  if (order) {
-    for (;;) {
-      const int k = atomicAdd(&ctr[0], 1);
-      if (k >= rows) return -1;
-      const int r = order[k];
-      if (r >= 0 && r < rows) return r;
-    }
-  }
+__device__ __forceinline__ int next_row(int32_t* ctr, int rows, int xcd, int& steal) {
   const int per = rows / 8, rem = rows % 8;
   while (steal < 8) {
     const int qd = (xcd + steal) & 7;
     const int beg = qd * per + min(qd, rem), n = per + (qd < rem ? 1 : 0);
     const int k = atomicAdd(&ctr[qd * 16], 1);
     if (k < n) return beg + k;
+    ++steal;
+  }
+  return -1;
+}
+
+// Queue of work units (thread 0 of a workgroup only): with `single`, one
+// counter walks the units in table order (the caller's row order); otherwise
+// XCD x drains its segment [seg[x], seg[x + 1]) of the table, then takes units
+// from the other segments in turn, as next_row.  Returns -1 once all is
+// drained.
+__device__ __forceinline__ int next_unit(int32_t* ctr, bool single, int n, const int32_t* __restrict__ seg, int xcd,
+                                         int& steal) {
+  if (single) {
+    const int k = atomicAdd(&ctr[0], 1);
+    return k < n ? k : -1;
+  }
+  while (steal < 8) {
+    const int qd = (xcd + steal) & 7;
+    const int beg = seg[qd], cnt = seg[qd + 1] - beg;
+    const int k = atomicAdd(&ctr[qd * 16], 1);
+    if (k < cnt) return beg + k;
     ++steal;
   }
   return -1;
@@ -727,20 +738,44 @@ __device__ __forceinline__ void exp_pairs(f32x16 (&s)[4], float c, float m, floa
   }
 }
 
-// One query-block row r of the 128-key-tile kernel.  LDS: smemK / smemV the K
-// and V^T tiles, smemKinfo (token variant) the key words of the current and
+// Partial result of a piece of a split row: query qi's O relative to 2^m,
+// unnormalised, [slot][query][D], and its running max and sums.
+template <int D>
+__device__ __forceinline__ void write_partial(const f32x16 (&oacc)[Geo<D>::D_TILES], float m, float lr_tot,
+                                              float l_tot, int slot, int qi, int half, float* __restrict__ part,
+                                              float* __restrict__ pstats) {
+  float* po = part + ((size_t)slot * kBQ + qi) * D;
+#pragma unroll
+  for (int dt = 0; dt < Geo<D>::D_TILES; ++dt)
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      *(float4*)(po + dt * 32 + 8 * g + 4 * half) =
+          make_float4(oacc[dt][4 * g], oacc[dt][4 * g + 1], oacc[dt][4 * g + 2], oacc[dt][4 * g + 3]);
+  if (half == 0) {
+    float* ps = pstats + (size_t)slot * 3 * kBQ;
+    ps[qi] = m;
+    ps[kBQ + qi] = lr_tot;
+    ps[2 * kBQ + qi] = l_tot;
+  }
+}
+
+// One work unit of row r of the 128-key-tile kernel: list positions [beg, end)
+// for the sparse (token) variant, written out or, with slot >= 0, left as a
+// partial result for the merge kernel (as k64_row); the whole row otherwise.
+// LDS: smemK / smemV the K and V^T tiles, smemKinfo (token variant) the key words of the current and
 // the next tile (a 1 KB copy each, of which the first 512 B are the tile's),
-// smemCols the row's key-block list (NB entries for the sparse variant), read
+// smemCols the unit's key-block list (up to NB entries for the sparse variant), read
 // once so that the tile loop issues no global loads of its own (a wait for one
 // would also drain the tiles in flight); the token variant then keeps each
 // query's thresholds by frame distance after it, [128][F] uint16.
 template <int D, bool SPARSE, bool PV, bool ENT, int TOK>
 __device__ __forceinline__ void bf16_row(
-    int r, uint8_t* smemK, uint8_t* smemV, uint8_t* smemKinfo, int32_t* smemCols,
+    int r, int beg, int end, int slot, uint8_t* smemK, uint8_t* smemV, uint8_t* smemKinfo, int32_t* smemCols,
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ ktile,
     const uint16_t* __restrict__ vtile, uint16_t* __restrict__ o, float* __restrict__ lse,
-    float* __restrict__ entropy, const int32_t* __restrict__ perm, const int32_t* __restrict__ cnt,
-    const int32_t* __restrict__ cols, int N, int n_pad, int NB, float scale_log2, const TokArgs& tk) {
+    float* __restrict__ entropy, const int32_t* __restrict__ perm, const int32_t* __restrict__ cols, int N,
+    int n_pad, int NB, float scale_log2, const TokArgs& tk, float* __restrict__ part,
+    float* __restrict__ pstats) {
   using G = Geo<D>;
   uint16_t* thrq = (uint16_t*)(smemCols + ((NB + 3) & ~3));
   const int bh = r / NB, u = r - bh * NB;
@@ -771,9 +806,9 @@ __device__ __forceinline__ void bf16_row(
       qf[kk] = __builtin_bit_cast(bf16x8, x);
     }
   }
-  const int count = SPARSE ? min(max(cnt[r], 0), NB) : NB;
+  const int count = SPARSE ? end - beg : NB;
   if constexpr (SPARSE) {
-    const int32_t* colp = cols + (size_t)r * NB;
+    const int32_t* colp = cols + (size_t)r * NB + beg;
     for (int j = t; j < count; j += kThreads) smemCols[j] = colp[j];
   }
   // token variant: this lane's query as a distance word and frame; a text
@@ -977,6 +1012,12 @@ __device__ __forceinline__ void bf16_row(
   const float l_tot = sum_halves(st.l);
   const float a_tot = ENT ? sum_halves(st.a) : 0.f;
   const float lr_tot = PV ? sum_halves(st.lr) : 0.f;
+  if constexpr (SPARSE && PV) {
+    if (slot >= 0) {
+      write_partial<D>(oacc, st.m, lr_tot, l_tot, slot, wave * 32 + col, half, part, pstats);
+      return;
+    }
+  }
   if (!qvalid) return;
   const size_t tok = (size_t)bh * N + qrow;
   if (PV) {
@@ -1002,16 +1043,18 @@ __device__ __forceinline__ void bf16_row(
 // TOK (sparse only): 0 block granular; 1 token mask with the 2-D distance,
 // 2 with the 1-D sequence distance (Eq. 15 inside the listed blocks); + 4 when
 // the plan has text tokens (text keys stay visible).
-// Persistent: as many workgroups as can be resident, each taking rows from the
-// row queue until it is drained (the first barrier of every row, after its list
-// is staged, orders the next s_row write after every wave's read).
+// Persistent: as many workgroups as can be resident, each taking rows (entropy
+// pass) or the units of the work-unit table (token variant, see
+// plan_units_kernel) until the queue is drained (the first barrier of every unit,
+// after its list is staged, orders the next s_row write after every wave's read).
 template <int D, bool SPARSE, bool PV, bool ENT, int OCC, int TOK = 0>
 __global__ __launch_bounds__(kThreads, OCC) void attn_bf16_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ ktile,
     const uint16_t* __restrict__ vtile, uint16_t* __restrict__ o, float* __restrict__ lse,
-    float* __restrict__ entropy, const int32_t* __restrict__ perm, const int32_t* __restrict__ cnt,
-    const int32_t* __restrict__ cols, const int32_t* __restrict__ order, int N, int n_pad, int NB,
-    int rows, float scale_log2, TokArgs tk, int32_t* __restrict__ ctr) {
+    float* __restrict__ entropy, const int32_t* __restrict__ perm, const int32_t* __restrict__ cols,
+    const int4* __restrict__ units, const int32_t* __restrict__ unit_hdr, bool ordered, int N, int n_pad, int NB,
+    int rows, float scale_log2, TokArgs tk, int32_t* __restrict__ ctr, float* __restrict__ part,
+    float* __restrict__ pstats) {
   constexpr int TILE = kBK * D * 2;
   __shared__ __attribute__((aligned(1024))) uint8_t smemK[TILE];
   __shared__ __attribute__((aligned(1024))) uint8_t smemV[PV ? TILE : 16];
@@ -1022,14 +1065,23 @@ __global__ __launch_bounds__(kThreads, OCC) void attn_bf16_kernel(
   for (;;) {
     if (threadIdx.x == 0) {
       int steal = s_steal;
-      s_row = next_row(ctr, SPARSE ? order : nullptr, rows, blockIdx.x & 7, steal);
+      s_row = SPARSE ? next_unit(ctr, ordered, unit_hdr[0], unit_hdr + 4, blockIdx.x & 7, steal)
+                     : next_row(ctr, rows, blockIdx.x & 7, steal);
       s_steal = steal;
     }
     __syncthreads();
-    const int r = s_row;
-    if (r < 0) break;
-    bf16_row<D, SPARSE, PV, ENT, TOK>(r, smemK, smemV, smemKinfo, smemCols, q, ktile, vtile, o, lse, entropy,
-                                      perm, cnt, cols, N, n_pad, NB, scale_log2, tk);
+    const int w = s_row;
+    if (w < 0) break;
+    int4 un = make_int4(w, 0, NB, -1);
+    if constexpr (SPARSE) {
+      un = units[w];
+      if (un.x < 0) {  // a placeholder unit: nothing to do
+        __syncthreads();
+        continue;
+      }
+    }
+    bf16_row<D, SPARSE, PV, ENT, TOK>(un.x, un.y, un.z, un.w, smemK, smemV, smemKinfo, smemCols, q, ktile, vtile, o,
+                                      lse, entropy, perm, cols, N, n_pad, NB, scale_log2, tk, part, pstats);
   }
 }
 
@@ -1264,21 +1316,7 @@ __device__ __forceinline__ void k64_row(
   const float lr_tot = sum_halves(st.lr);
   const float l_tot = LSE ? sum_halves(st.l) : 0.f;
   if (SPARSE && slot >= 0) {
-    // a piece of a split row: O relative to 2^m, unnormalised, [slot][query][D]
-    const int qi = wave * 32 + col;
-    float* po = part + ((size_t)slot * kBQ + qi) * D;
-#pragma unroll
-    for (int dt = 0; dt < G::D_TILES; ++dt)
-#pragma unroll
-      for (int g = 0; g < 4; ++g)
-        *(float4*)(po + dt * 32 + 8 * g + 4 * half) =
-            make_float4(oacc[dt][4 * g], oacc[dt][4 * g + 1], oacc[dt][4 * g + 2], oacc[dt][4 * g + 3]);
-    if (half == 0) {
-      float* ps = pstats + (size_t)slot * 3 * kBQ;
-      ps[qi] = st.m;
-      ps[kBQ + qi] = lr_tot;
-      ps[2 * kBQ + qi] = l_tot;
-    }
+    write_partial<D>(oacc, st.m, lr_tot, l_tot, slot, wave * 32 + col, half, part, pstats);
     return;
   }
   if (!qvalid) return;
@@ -1296,27 +1334,6 @@ __device__ __forceinline__ void k64_row(
       *(uint2*)(dst + d0) = w;
     }
   if (LSE && half == 0) lse[tok] = l_tot > 0.f ? 0.69314718055994531f * (st.m + __log2f(l_tot)) : -INFINITY;
-}
-
-// Queue of work units (thread 0 of a workgroup only): with `single`, one
-// counter walks the units in table order (the caller's row order); otherwise
-// XCD x drains its segment [seg[x], seg[x + 1]) of the table, then takes units
-// from the other segments in turn, as next_row.  Returns -1 once all is
-// drained.
-__device__ __forceinline__ int next_unit(int32_t* ctr, bool single, int n, const int32_t* __restrict__ seg, int xcd,
-                                         int& steal) {
-  if (single) {
-    const int k = atomicAdd(&ctr[0], 1);
-    return k < n ? k : -1;
-  }
-  while (steal < 8) {
-    const int qd = (xcd + steal) & 7;
-    const int beg = seg[qd], cnt = seg[qd + 1] - beg;
-    const int k = atomicAdd(&ctr[qd * 16], 1);
-    if (k < cnt) return beg + k;
-    ++steal;
-  }
-  return -1;
 }
 
 // Persistent kernel: as many workgroups as fit on the GPU (three per CU), each
@@ -1342,7 +1359,7 @@ __global__ __launch_bounds__(kThreads, 3) void attn_k64_kernel(
     if (threadIdx.x == 0) {
       int steal = s_steal;
       s_row = SPARSE ? next_unit(ctr, ordered, n_work, unit_hdr + 4, blockIdx.x & 7, steal)
-                     : next_row(ctr, nullptr, rows, blockIdx.x & 7, steal);
+                     : next_row(ctr, rows, blockIdx.x & 7, steal);
       s_steal = steal;
     }
     __syncthreads();
@@ -1363,7 +1380,10 @@ __global__ __launch_bounds__(kThreads, 3) void attn_k64_kernel(
   }
 }
 
-// Work units of a block-sparse call (one workgroup of 1024 threads).  With T
+// Work units of a block-sparse or token-level call (one workgroup of 1024
+// threads).  (The token call on whole rows ended on its longest ones: 30 x 52 x
+// 21 frames, 12 heads at 15 % of the block pairs, 21 of 3,072 rows keeping all
+// 256 blocks, took 2.00 ms, on units 1.23 ms.)  With T
 // the total list length and G the attention grid, L = max(kSplitMin, ceil(T /
 // (G kSplitPerWG))) (doubled while the pieces would exceed the workspace's
 // partial slots, which its capacity, 2 G kSplitPerWG + 1 slots, rules out),
@@ -1706,6 +1726,25 @@ int k64_sparse_grid_cap_d(const tra_plan_s& p) {
   return std::max(1, std::max(a, b)) * std::max(p.n_cu, 1);
 }
 
+// Work units of a block-sparse or token-level call for `grid` workgroups, and
+// the merge of its split rows.
+void launch_plan_units(const tra_plan_s& p, const AttnArgs& a, int grid, hipStream_t s) {
+  hipLaunchKernelGGL(plan_units_kernel, dim3(1), dim3(1024), 0, s, a.cnt, a.order, p.rows, p.NB, grid,
+                     (int4*)p.d_units, p.units_cap, (int4*)p.d_splits, p.splits_cap, p.slots_cap, p.d_unit_hdr,
+                     p.d_row_ctr);
+}
+
+template <int D>
+void launch_merge(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
+  const dim3 grid(std::max(1, std::min(p.splits_cap, 1024)));
+  if (a.lse)
+    hipLaunchKernelGGL((merge_split_rows_kernel<D, true>), grid, dim3(256), 0, s, (const int4*)p.d_splits,
+                       p.d_unit_hdr, p.d_part, p.d_pstats, (uint16_t*)a.o, a.lse, p.d_perm, p.S, p.NB);
+  else
+    hipLaunchKernelGGL((merge_split_rows_kernel<D, false>), grid, dim3(256), 0, s, (const int4*)p.d_splits,
+                       p.d_unit_hdr, p.d_part, p.d_pstats, (uint16_t*)a.o, a.lse, p.d_perm, p.S, p.NB);
+}
+
 template <int D, bool SPARSE, bool LSE>
 void launch_k64_lse(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
   const float scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)D));
@@ -1713,9 +1752,7 @@ void launch_k64_lse(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
   int grid = resident_grid(attn_k64_kernel<D, SPARSE, LSE>, lds_bytes, p);
   if (SPARSE) {
     grid = std::min(grid, p.split_wg_cap);
-    hipLaunchKernelGGL(plan_units_kernel, dim3(1), dim3(1024), 0, s, a.cnt, a.order, p.rows, p.NB, grid,
-                       (int4*)p.d_units, p.units_cap, (int4*)p.d_splits, p.splits_cap, p.slots_cap, p.d_unit_hdr,
-                       p.d_row_ctr);
+    launch_plan_units(p, a, grid, s);
   } else {
     hipLaunchKernelGGL(reset_row_counters, dim3(1), dim3(kRowCounters), 0, s, p.d_row_ctr);
   }
@@ -1726,10 +1763,7 @@ void launch_k64_lse(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
                      p.d_unit_hdr, a.order != nullptr, p.S, p.n_pad, p.NB, p.rows, scale_log2, p.d_row_ctr,
                      p.d_part, p.d_pstats);
   if (a.ev_stop) (void)hipEventRecord(a.ev_stop, s);
-  if (SPARSE)
-    hipLaunchKernelGGL((merge_split_rows_kernel<D, LSE>), dim3(std::max(1, std::min(p.splits_cap, 1024))),
-                       dim3(256), 0, s, (const int4*)p.d_splits, p.d_unit_hdr, p.d_part, p.d_pstats,
-                       (uint16_t*)a.o, a.lse, p.d_perm, p.S, p.NB);
+  if (SPARSE) launch_merge<D>(p, a, s);
 }
 
 template <int D, bool SPARSE>
@@ -1960,7 +1994,7 @@ __global__ __launch_bounds__(kFusedThreads, 1) void attn_fused_kernel(
   for (;;) {
     if (threadIdx.x == 0) {
       int steal = s_steal;
-      s_row = next_row(ctr, nullptr, rows, blockIdx.x & 7, steal);
+      s_row = next_row(ctr, rows, blockIdx.x & 7, steal);
       s_steal = steal;
     }
     __syncthreads();
@@ -1989,13 +2023,20 @@ void launch_variant(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
   if (TOK != 0) lds_bytes += (size_t)kBQ * p.cfg.frames * sizeof(uint16_t);
   const TokArgs tk{a.radius_sq, p.cfg.distance == TRA_DIST_1D ? p.d_thr1 : p.d_thr, p.d_kinfo, p.d_blocks,
                    p.d_coord, p.d_kfeat, p.N, p.cfg.frames, p.n_cap};
-  const int grid = resident_grid(attn_bf16_kernel<D, SPARSE, PV, ENT, 2, TOK>, lds_bytes, p);
-  hipLaunchKernelGGL(reset_row_counters, dim3(1), dim3(kRowCounters), 0, s, p.d_row_ctr);
+  int grid = resident_grid(attn_bf16_kernel<D, SPARSE, PV, ENT, 2, TOK>, lds_bytes, p);
+  if (SPARSE) {
+    grid = std::min(grid, p.split_wg_cap);
+    launch_plan_units(p, a, grid, s);
+  } else {
+    hipLaunchKernelGGL(reset_row_counters, dim3(1), dim3(kRowCounters), 0, s, p.d_row_ctr);
+  }
   if (a.ev_start) (void)hipEventRecord(a.ev_start, s);
   hipLaunchKernelGGL((attn_bf16_kernel<D, SPARSE, PV, ENT, 2, TOK>), dim3(grid), dim3(kThreads), lds_bytes, s,
-                     (const uint16_t*)a.q, p.d_kt, p.d_vt, (uint16_t*)a.o, a.lse, a.entropy, p.d_perm,
-                     a.cnt, a.cols, a.order, p.S, p.n_pad, p.NB, p.rows, scale_log2, tk, p.d_row_ctr);
+                     (const uint16_t*)a.q, p.d_kt, p.d_vt, (uint16_t*)a.o, a.lse, a.entropy, p.d_perm, a.cols,
+                     (const int4*)p.d_units, p.d_unit_hdr, a.order != nullptr, p.S, p.n_pad, p.NB, p.rows,
+                     scale_log2, tk, p.d_row_ctr, p.d_part, p.d_pstats);
   if (a.ev_stop) (void)hipEventRecord(a.ev_stop, s);
+  if (SPARSE) launch_merge<D>(p, a, s);
 }
 
 template <int D>

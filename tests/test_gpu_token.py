@@ -124,6 +124,29 @@ def test_token_full_radius_matches_sparse(name):
     assert lerr <= 1e-4 + 1e-5 * run.lse_sp.abs().max().item(), f"token vs sparse lse {lerr:.3e}"
 
 
+@pytest.mark.parametrize("head_dim,text", [(128, 0), (64, 40)])
+@pytest.mark.parametrize("radius", [None, 120])
+def test_token_split_rows(head_dim, text, radius):
+    """Rows of more than 48 blocks (61 or 62 here, lists that keep every block)
+    are cut into pieces and merged: outputs against the oracle under the
+    method's own radii and under short forced ones, where a query covers no key
+    of some pieces, and bitwise the same under a row order."""
+    _gpu()
+    import torch
+    w = synth.Workload("token_split", 1, 1, head_dim, "bf16", 5, 30, 52, 128, 0.25, 4.0, 0.6, seed=88,
+                       tile_h=8, tile_w=16, text_tokens=text)
+    run = Run(w, rule="union", radius_override=radius)
+    NB = run.plan.n_blocks
+    run.mask.fill_(1)
+    run.cnt.fill_(NB)
+    run.cols.copy_(torch.arange(NB, dtype=torch.int32, device="cuda").expand_as(run.cols))
+    assert NB > 48
+    o, lse = _token_call(run)
+    _check_against_oracle(run, o, lse, TOL_O_BF16)
+    o2, lse2 = _token_call(run, order=torch.arange(NB - 1, -1, -1, dtype=torch.int32, device="cuda"))
+    assert torch.equal(o, o2) and torch.equal(lse, lse2)
+
+
 @pytest.mark.parametrize("name", ["ragged_bf16_d128", "tiny"])
 def test_token_out_of_range_column_ids_are_skipped(name):
     """Lists padded with -1 / NB entries give the same output as clean lists."""
