@@ -210,7 +210,7 @@ tra_status tra_plan_create(const tra_config* cfg, tra_plan* out) {
 
     tra::HostTables t;
     const bool one_d = cfg->distance == TRA_DIST_1D;
-    tra::build_host_tables(*cfg, &t, true, true, one_d, true, cfg->dtype == TRA_BF16);
+    tra::build_host_tables(*cfg, &t, true, true, one_d, true, true);
 
     tra_plan p = new tra_plan_s();
     p->cfg = *cfg;
@@ -278,18 +278,18 @@ tra_status tra_plan_create(const tra_config* cfg, tra_plan* out) {
       tra_plan_destroy(p);
       return fail(TRA_ERR_ALLOC, std::string("plan count table: ") + hipGetErrorString(e));
     }
+    if (!t.kfeat.empty()) {
+      const size_t bytes = t.kfeat.size() * sizeof(uint16_t);
+      if ((e = hipMalloc((void**)&p->d_kfeat, bytes)) != hipSuccess ||
+          (e = hipMemcpy(p->d_kfeat, t.kfeat.data(), bytes, hipMemcpyHostToDevice)) != hipSuccess) {
+        tra_plan_destroy(p);
+        return fail(TRA_ERR_ALLOC, std::string("plan key-feature table: ") + hipGetErrorString(e));
+      }
+    }
     if (cfg->dtype == TRA_BF16) {
       if ((e = upload(&p->d_kinfo, t.kinfo)) != hipSuccess) {
         tra_plan_destroy(p);
         return fail(TRA_ERR_ALLOC, std::string("plan key-info table: ") + hipGetErrorString(e));
-      }
-      if (!t.kfeat.empty()) {
-        const size_t bytes = t.kfeat.size() * sizeof(uint16_t);
-        if ((e = hipMalloc((void**)&p->d_kfeat, bytes)) != hipSuccess ||
-            (e = hipMemcpy(p->d_kfeat, t.kfeat.data(), bytes, hipMemcpyHostToDevice)) != hipSuccess) {
-          tra_plan_destroy(p);
-          return fail(TRA_ERR_ALLOC, std::string("plan key-feature table: ") + hipGetErrorString(e));
-        }
       }
       p->split_wg_cap = tra::k64_sparse_grid_cap(*p);
       tra::split_capacities(p->split_wg_cap, p->rows, p->NB, cfg->head_dim, &p->units_cap, &p->splits_cap,

@@ -100,9 +100,9 @@ struct tra_plan_s {
   // raster index) with a second-frame flag and a text flag, [NB + 1][128],
   // the key side of the token mask inside a tile.
   int32_t* d_kinfo = nullptr;
-  // bf16 plans with the 2-D distance: per key, 8 f16 integers b with
+  // plans with the 2-D distance: per key, 8 f16 integers b with
   // a_i . b_j = T_i(frame of j) - D_ij for the query vector a_i the token
-  // kernel forms per tile, [NB][2][128][4] (see build_host_tables).
+  // and mask kernels form, [NB][2][block][4] (see build_host_tables).
   uint16_t* d_kfeat = nullptr;
   int32_t thr_max = 0;  // largest entry of the plan's threshold table
   // bf16 plans, call workspace: row-queue counters of the persistent attention
