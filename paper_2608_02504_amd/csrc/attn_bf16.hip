@@ -10,8 +10,8 @@
 //                     splitting the keys of one query block.
 //
 // Layout pre-pass
-//   K and V are first gathered into tile-major order (Sec. 3.3: tokens of a
-//   spatial tile become contiguous) in the call's workspace, one 128-token key
+//   K and V are first rewritten in tile-major order (Sec. 3.3: tokens of a
+//   spatial tile become contiguous) in the call's workspace (prep_kernel), one 128-token key
 //   block = one contiguous tile, padding positions zero-filled: K as 128 rows x D,
 //   V transposed (D rows x 128 keys), so that both matrix operands are read
 //   from LDS with plain 16-byte reads.  The attention loop then addresses
@@ -29,7 +29,7 @@
 //   token-level calls take work units instead of rows: long rows are cut into pieces whose
 //   partial results a merge kernel combines, and each XCD's segment of the
 //   unit table lists its split pieces first, piece-major, so that the
-//   workgroups of one XCD walk the same key range (see plan_units_kernel).
+//   workgroups of one XCD walk the same key range (see plan_units).
 //
 // Per tile (split barriers)
 //   K and V^T go from HBM straight into LDS (global_load_lds_dwordx4 from a
@@ -98,66 +98,6 @@ __device__ __forceinline__ void wait_vm() {
 // established with explicit vmcnt waits before the barrier.
 __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
-// ------------------------------------------------------------ layout pre-pass
-// Both gathers take (batch, head) pairs bh = blockIdx.y, blockIdx.y + gridDim.y, ...
-// (the grid's y extent is capped at kGatherMaxY).
-constexpr int kGatherMaxY = 65535;
-
-// kt[bh][p][:] = k[bh][perm[p]][:], 0 where perm[p] < 0 (a padding position).
-// Grid: (16-byte chunks of one head / 256, pairs); thread = one chunk.
-template <int D>
-__global__ __launch_bounds__(256) void gather_k_kernel(const uint4* __restrict__ k, uint4* __restrict__ kt,
-                                                       const int32_t* __restrict__ perm, int N, int n_pad,
-                                                       int bhs) {
-  constexpr int CH = D / 8;
-  const int idx = blockIdx.x * 256 + threadIdx.x;  // < n_pad * CH < 2^24
-  if (idx >= n_pad * CH) return;
-  const int p = idx / CH, c = idx % CH;
-  const int tok = perm[p];
-  for (size_t bh = blockIdx.y; bh < (size_t)bhs; bh += gridDim.y)
-    kt[bh * n_pad * CH + idx] = tok >= 0 ? k[(bh * N + tok) * CH + c] : make_uint4(0, 0, 0, 0);
-}
-
-// V transposed per key block, tile-major: for tile-major position p = 128 b + j,
-// vt[bh][b][d][j] = v[bh][perm[p]][d] (0 at a padding position), so key block b of a
-// head is one contiguous D x 128 tile with the key index fastest.  One
-// workgroup per 64 positions (of one pair at a time), through LDS.
-template <int D>
-__global__ __launch_bounds__(256) void gather_vt_kernel(const uint16_t* __restrict__ v,
-                                                        uint16_t* __restrict__ vt,
-                                                        const int32_t* __restrict__ perm, int N,
-                                                        int n_pad, int bhs) {
-  constexpr int TOK = 64, CH = D / 8, LS = D + 2;
-  __shared__ uint16_t tile[TOK * LS];
-  const int p0 = blockIdx.x * TOK, t = threadIdx.x;
-  for (int bh = blockIdx.y; bh < bhs; bh += gridDim.y) {
-    __syncthreads();  // the previous pair's reads of the tile are done
-    for (int i = t; i < TOK * CH; i += 256) {
-      const int j = i / CH, c = i - j * CH;
-      uint4 x = make_uint4(0, 0, 0, 0);
-      const int tok = perm[p0 + j];
-      if (tok >= 0) x = *(const uint4*)(v + ((size_t)bh * N + tok) * D + c * 8);
-      const uint32_t w[4] = {x.x, x.y, x.z, x.w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        tile[j * LS + c * 8 + 2 * e] = (uint16_t)(w[e] & 0xFFFFu);
-        tile[j * LS + c * 8 + 2 * e + 1] = (uint16_t)(w[e] >> 16);
-      }
-    }
-    __syncthreads();
-    for (int i = t; i < D * (TOK / 8); i += 256) {
-      const int d = i / (TOK / 8), tc = i - d * (TOK / 8);
-      uint32_t w[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        w[e] = (uint32_t)tile[(tc * 8 + 2 * e) * LS + d] | ((uint32_t)tile[(tc * 8 + 2 * e + 1) * LS + d] << 16);
-      const int p = p0 + tc * 8;
-      *(uint4*)(vt + (size_t)bh * n_pad * D + ((size_t)(p / kBK) * D + d) * kBK + p % kBK) =
-          make_uint4(w[0], w[1], w[2], w[3]);
-    }
-  }
 }
 
 // ------------------------------------------------------------ attention
@@ -552,17 +492,30 @@ __device__ __forceinline__ int next_row(int32_t* ctr, int rows, int xcd, int& st
   return -1;
 }
 
-// Queue of work units (thread 0 of a workgroup only): with `single`, one
-// counter walks the units in table order (the caller's row order); otherwise
-// XCD x drains its segment [seg[x], seg[x + 1]) of the table, then takes units
-// from the other segments in turn, as next_row.  Returns -1 once all is
-// drained.
-__device__ __forceinline__ int next_unit(int32_t* ctr, bool single, int n, const int32_t* __restrict__ seg, int xcd,
-                                         int& steal) {
-  if (single) {
+// Work of a block-sparse or token-level call: the units of the work-unit table
+// (see plan_units), or, on plans whose rows are never cut (units NULL), the rows.
+// (The kernels take the pointers as __restrict__ arguments of their own, which
+// lets the compiler read the tables through the scalar cache: as members of one
+// struct argument they cost 2-4 % of a 480p call in vector loads per claim.)
+struct WorkArgs {
+  const int32_t* cnt;    // [rows] list lengths
+  const int32_t* order;  // the caller's row order, or NULL
+  const int4* units;
+  const int32_t* hdr;
+  int rows, NB;
+};
+
+// Queue of that work (thread 0 of a workgroup only).  With the caller's order,
+// one counter walks the table (or the order); otherwise XCD x drains its segment
+// [seg[x], seg[x + 1]) of the table (or of the rows), then takes work from the
+// other segments in turn, as next_row.  Returns -1 once all is drained.
+__device__ __forceinline__ int next_work(int32_t* ctr, const WorkArgs& a, int xcd, int& steal) {
+  if (a.order) {
     const int k = atomicAdd(&ctr[0], 1);
-    return k < n ? k : -1;
+    return k < (a.units ? a.hdr[0] : a.rows) ? k : -1;
   }
+  if (!a.units) return next_row(ctr, a.rows, xcd, steal);
+  const int32_t* seg = a.hdr + 4;
   while (steal < 8) {
     const int qd = (xcd + steal) & 7;
     const int beg = seg[qd], cnt = seg[qd + 1] - beg;
@@ -573,12 +526,20 @@ __device__ __forceinline__ int next_unit(int32_t* ctr, bool single, int n, const
   return -1;
 }
 
-// Zeroes the row-queue counters (a kernel rather than a memset, so that the
-// launch sequence also replays correctly inside a captured graph).
-__global__ void reset_row_counters(int32_t* ctr) {
-  if (threadIdx.x < kRowCounters) ctr[threadIdx.x] = 0;
+// Work item w as {row, list begin, list end, partial slot or -1}; row -1: nothing
+// to do (a placeholder unit, or an order entry outside [0, rows)).
+// (The same in every lane: kept in scalar registers.)
+__device__ __forceinline__ int4 work_at(const WorkArgs& a, int w) {
+  int4 un = make_int4(-1, 0, 0, -1);
+  if (a.units) {
+    un = a.units[w];
+  } else {
+    const int r = a.order ? a.order[w] : w;
+    if (r >= 0 && r < a.rows) un = make_int4(r, 0, min(max(a.cnt[r], 0), a.NB), -1);
+  }
+  return make_int4(__builtin_amdgcn_readfirstlane(un.x), __builtin_amdgcn_readfirstlane(un.y),
+                   __builtin_amdgcn_readfirstlane(un.z), __builtin_amdgcn_readfirstlane(un.w));
 }
-
 
 // ------------------------------------------------------------ softmax and copy helpers
 // Row max of a score tile as a max3 tree (short dependency chains), folded into
@@ -1045,16 +1006,17 @@ __device__ __forceinline__ void bf16_row(
 // the plan has text tokens (text keys stay visible).
 // Persistent: as many workgroups as can be resident, each taking rows (entropy
 // pass) or the units of the work-unit table (token variant, see
-// plan_units_kernel) until the queue is drained (the first barrier of every unit,
+// plan_units) until the queue is drained (the first barrier of every unit,
 // after its list is staged, orders the next s_row write after every wave's read).
 template <int D, bool SPARSE, bool PV, bool ENT, int OCC, int TOK = 0>
 __global__ __launch_bounds__(kThreads, OCC) void attn_bf16_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ ktile,
     const uint16_t* __restrict__ vtile, uint16_t* __restrict__ o, float* __restrict__ lse,
-    float* __restrict__ entropy, const int32_t* __restrict__ perm, const int32_t* __restrict__ cols,
-    const int4* __restrict__ units, const int32_t* __restrict__ unit_hdr, bool ordered, int N, int n_pad, int NB,
-    int rows, float scale_log2, TokArgs tk, int32_t* __restrict__ ctr, float* __restrict__ part,
-    float* __restrict__ pstats) {
+    float* __restrict__ entropy, const int32_t* __restrict__ perm, const int32_t* __restrict__ cnt,
+    const int32_t* __restrict__ cols, const int32_t* __restrict__ order, const int4* __restrict__ units,
+    const int32_t* __restrict__ unit_hdr, int N, int n_pad, int NB, int rows, float scale_log2, TokArgs tk,
+    int32_t* __restrict__ ctr, float* __restrict__ part, float* __restrict__ pstats) {
+  const WorkArgs wk{cnt, order, units, unit_hdr, rows, NB};
   constexpr int TILE = kBK * D * 2;
   __shared__ __attribute__((aligned(1024))) uint8_t smemK[TILE];
   __shared__ __attribute__((aligned(1024))) uint8_t smemV[PV ? TILE : 16];
@@ -1065,17 +1027,16 @@ __global__ __launch_bounds__(kThreads, OCC) void attn_bf16_kernel(
   for (;;) {
     if (threadIdx.x == 0) {
       int steal = s_steal;
-      s_row = SPARSE ? next_unit(ctr, ordered, unit_hdr[0], unit_hdr + 4, blockIdx.x & 7, steal)
-                     : next_row(ctr, rows, blockIdx.x & 7, steal);
+      s_row = SPARSE ? next_work(ctr, wk, blockIdx.x & 7, steal) : next_row(ctr, wk.rows, blockIdx.x & 7, steal);
       s_steal = steal;
     }
     __syncthreads();
-    const int w = s_row;
+    const int w = __builtin_amdgcn_readfirstlane(s_row);
     if (w < 0) break;
     int4 un = make_int4(w, 0, NB, -1);
     if constexpr (SPARSE) {
-      un = units[w];
-      if (un.x < 0) {  // a placeholder unit: nothing to do
+      un = work_at(wk, w);
+      if (un.x < 0) {
         __syncthreads();
         continue;
       }
@@ -1338,36 +1299,36 @@ __device__ __forceinline__ void k64_row(
 
 // Persistent kernel: as many workgroups as fit on the GPU (three per CU), each
 // taking work from a queue until it is drained: rows (dense), or the units of
-// the work-unit table (block-sparse; see plan_units_kernel).  Every unit starts
+// the work-unit table (block-sparse; see plan_units).  Every unit starts
 // with a workgroup barrier (after its block list is staged), which also orders
 // the next s_row write after every wave's read of the current one.
 template <int D, bool SPARSE, bool LSE>
 __global__ __launch_bounds__(kThreads, 3) void attn_k64_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ ktile, const uint16_t* __restrict__ vtile,
     uint16_t* __restrict__ o, float* __restrict__ lse, const int32_t* __restrict__ perm,
-    const int32_t* __restrict__ cols, const int32_t* __restrict__ bcount, const int4* __restrict__ units,
-    const int32_t* __restrict__ unit_hdr, bool ordered, int N, int n_pad, int NB, int rows, float scale_log2,
-    int32_t* __restrict__ ctr, float* __restrict__ part, float* __restrict__ pstats) {
+    const int32_t* __restrict__ cnt, const int32_t* __restrict__ cols, const int32_t* __restrict__ order,
+    const int32_t* __restrict__ bcount, const int4* __restrict__ units, const int32_t* __restrict__ unit_hdr, int N,
+    int n_pad, int NB, int rows, float scale_log2, int32_t* __restrict__ ctr, float* __restrict__ part,
+    float* __restrict__ pstats) {
+  const WorkArgs wk{cnt, order, units, unit_hdr, rows, NB};
   constexpr int KT_BYTES = kKT * D * 2;
   __shared__ __attribute__((aligned(1024))) uint8_t smemK[KT_BYTES];
   __shared__ __attribute__((aligned(1024))) uint8_t smemV[KT_BYTES];
   extern __shared__ int32_t smemCols[];
   __shared__ int s_row, s_steal;  // thread 0's queue state lives in LDS, not in a register
-  const int n_work = SPARSE ? unit_hdr[0] : rows;
   if (threadIdx.x == 0) s_steal = 0;
   for (;;) {
     if (threadIdx.x == 0) {
       int steal = s_steal;
-      s_row = SPARSE ? next_unit(ctr, ordered, n_work, unit_hdr + 4, blockIdx.x & 7, steal)
-                     : next_row(ctr, rows, blockIdx.x & 7, steal);
+      s_row = SPARSE ? next_work(ctr, wk, blockIdx.x & 7, steal) : next_row(ctr, wk.rows, blockIdx.x & 7, steal);
       s_steal = steal;
     }
     __syncthreads();
-    const int w = s_row;
+    const int w = __builtin_amdgcn_readfirstlane(s_row);
     if (w < 0) break;
     if constexpr (SPARSE) {
-      const int4 un = units[w];
-      if (un.x < 0) {  // a placeholder unit (never written by a consistent plan): nothing to do
+      const int4 un = work_at(wk, w);
+      if (un.x < 0) {
         __syncthreads();
         continue;
       }
@@ -1412,40 +1373,64 @@ __global__ __launch_bounds__(kThreads, 3) void attn_k64_kernel(
 //
 // Writes units[U] = {row, list begin, list end, slot or -1} (row -1: a
 // placeholder), splits[P] = {row, first slot, pieces, 0} and hdr = {U, P, L,
-// 0, segment starts x 9}, and zeroes the attention kernel's queue counters.  A split row has c / L < pieces < 2 c / L, so P <= T
+// 0, segment starts x 9}.  A split row has c / L < pieces < 2 c / L, so P <= T
 // / L <= G kSplitPerWG; with the placeholders U <= rows + max(G kSplitPerWG,
 // ceil(NB / kSplitMin) slots / 2): the call's workspace holds tables of these
 // bounds (entries past a capacity are never written).
 constexpr int kSplitPerWG = 16;
 constexpr int kSplitMin = 48;
-constexpr int kPlanStagedRows = 32768;  // rows whose lengths plan_units_kernel keeps in LDS (64 KB)
+constexpr int kPlanStagedRows = 32768;   // rows whose lengths plan_units keeps in LDS (64 KB)
 constexpr int kTailDiv = 8;              // the tail: the last eighth of a segment's whole rows
 constexpr int kTailBins = 256;           // length buckets of the tail's order
 
 // Length bucket of a whole row (0 <= c <= L) in the tail's order.
 __device__ __forceinline__ int tail_bin(int c, int L) { return min(kTailBins - 1, c * kTailBins / (L + 1)); }
 
-__global__ __launch_bounds__(1024) void plan_units_kernel(const int32_t* __restrict__ cnt,
-                                                          const int32_t* __restrict__ order, int rows, int NB,
-                                                          int n_wg, int4* __restrict__ units, int units_cap,
-                                                          int4* __restrict__ splits, int splits_cap,
-                                                          int slots_cap, int32_t* __restrict__ hdr,
-                                                          int32_t* __restrict__ ctr) {
-  __shared__ long long s_red[1024];
-  __shared__ int s_scan[3][1024];
-  __shared__ int s_seg[4][1024];  // per thread, segmented: split rows, other rows, max pieces
-  __shared__ int s_base[9];
-  __shared__ int s_tail[8][kTailBins];  // per segment: tail rows per length bucket, then their slots
-  __shared__ uint16_t s_len[kPlanStagedRows];  // the row lengths, read once with coalesced loads
-  const int t = threadIdx.x;
-  if (t < kRowCounters) ctr[t] = 0;  // the attention kernel's queue counters, zeroed here for it
+struct PlanArgs {
+  const int32_t* cnt;    // NULL: the call has no work units, only the counters are zeroed
+  const int32_t* order;
+  int rows, NB, n_wg, units_cap, splits_cap, slots_cap;
+  int4* units;
+  int4* splits;
+  int32_t* hdr;
+  int32_t* ctr;
+};
+
+constexpr int kPrepThreads = 1024;
+constexpr int kPrepWaves = kPrepThreads / 64;
+// LDS of plan_units: tail buckets, per-wave totals, segment starts, row lengths
+constexpr int kPlanTailInts = 8 * kTailBins, kPlanWaveInts = kPrepWaves * 8, kPlanBaseInts = 16;
+constexpr size_t plan_lds_bytes(int rows) {
+  return (kPlanTailInts + kPlanWaveInts + kPlanBaseInts) * sizeof(int) +
+         (rows <= kPlanStagedRows ? (size_t)rows * sizeof(uint16_t) : 0);
+}
+
+// Inclusive scan of x over a wave.
+__device__ __forceinline__ int wave_scan(int x, int lane) {
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(x, o);
+    if (lane >= o) x += y;
+  }
+  return x;
+}
+
+__device__ void plan_units(const PlanArgs& a, uint8_t* lds) {
+  int* s_tail = (int*)lds;  // [8][kTailBins] per segment: tail rows per length bucket, then their slots
+  int* s_wave = s_tail + kPlanTailInts;
+  int* s_base = s_wave + kPlanWaveInts;
+  uint16_t* s_len = (uint16_t*)(s_base + kPlanBaseInts);  // the row lengths, read once with coalesced loads
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int rows = a.rows, NB = a.NB;
+  const int32_t* cnt = a.cnt;
+  const int32_t* order = a.order;
   const bool segmented = order == nullptr;
   // (each thread's walk below is a contiguous range of rows, which would read
   // the counts with one dependent-latency load per row in every pass)
   const bool staged = rows <= kPlanStagedRows;
   if (staged) {
 #pragma unroll 8
-    for (int r = t; r < rows; r += 1024) s_len[r] = (uint16_t)min(max(cnt[r], 0), NB);
+    for (int r = t; r < rows; r += kPrepThreads) s_len[r] = (uint16_t)min(max(cnt[r], 0), NB);
     __syncthreads();
   }
   // this thread's positions [k0, k1) of the walk: in segment t / 128 for the
@@ -1458,7 +1443,7 @@ __global__ __launch_bounds__(1024) void plan_units_kernel(const int32_t* __restr
     k0 = min(r1, r0 + ls * per);
     k1 = min(r1, k0 + per);
   } else {
-    const int per = (rows + 1023) / 1024;
+    const int per = (rows + kPrepThreads - 1) / kPrepThreads;
     k0 = min(rows, t * per);
     k1 = min(rows, k0 + per);
   }
@@ -1466,16 +1451,21 @@ __global__ __launch_bounds__(1024) void plan_units_kernel(const int32_t* __restr
   auto len_of = [&](int r) {
     return (r >= 0 && r < rows) ? (staged ? (int)s_len[r] : min(max(cnt[r], 0), NB)) : -1;
   };
+  auto block_sum = [&](long long x) {
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) x += __shfl_xor(x, o);
+    __syncthreads();
+    if (lane == 0) ((long long*)s_wave)[wave] = x;
+    __syncthreads();
+    x = 0;
+#pragma unroll
+    for (int w = 0; w < kPrepWaves; ++w) x += ((const long long*)s_wave)[w];
+    return x;
+  };
   long long tot = 0;
   for (int k = k0; k < k1; ++k) tot += max(len_of(row_at(k)), 0);
-  s_red[t] = tot;
-  __syncthreads();
-  for (int st = 512; st > 0; st >>= 1) {
-    if (t < st) s_red[t] += s_red[t + st];
-    __syncthreads();
-  }
-  const long long total = s_red[0];
-  const long long share = (long long)max(n_wg, 1) * kSplitPerWG;
+  const long long total = block_sum(tot);
+  const long long share = (long long)max(a.n_wg, 1) * kSplitPerWG;
   int L = (int)max((long long)kSplitMin, (total + share - 1) / share);
   // per thread: units, slots and split rows of its positions; L doubles until
   // the pieces of the split rows fit the partial slots
@@ -1495,148 +1485,218 @@ __global__ __launch_bounds__(1024) void plan_units_kernel(const int32_t* __restr
         ++nw;
       }
     }
-    __syncthreads();
-    s_red[t] = ns;
-    __syncthreads();
-    for (int st = 512; st > 0; st >>= 1) {
-      if (t < st) s_red[t] += s_red[t + st];
-      __syncthreads();
-    }
-    if (s_red[0] <= slots_cap || L >= NB) break;
+    if (block_sum(ns) <= a.slots_cap || L >= NB) break;
     L = min(2 * L, NB);
   }
-  s_scan[0][t] = nu;
-  s_scan[1][t] = ns;
-  s_scan[2][t] = np;
-  s_seg[0][t] = np;
-  s_seg[1][t] = nw;
-  s_seg[2][t] = pmx;
+  // exclusive prefixes over the workgroup, and inside the 128-thread segments
+  // (two waves each): wave scans, then the other waves' totals
+  const int nu_i = wave_scan(nu, lane), ns_i = wave_scan(ns, lane), np_i = wave_scan(np, lane),
+            nw_i = wave_scan(nw, lane);
+  int pm = pmx;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) pm = max(pm, __shfl_xor(pm, o));
   __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {  // inclusive scans; s_seg within 128-thread segments
-    int a0 = 0, a1 = 0, a2 = 0, g0 = 0, g1 = 0, g2 = 0;
-    if (t >= off) {
-      a0 = s_scan[0][t - off];
-      a1 = s_scan[1][t - off];
-      a2 = s_scan[2][t - off];
-    }
-    if ((t & 127) >= off) {
-      g0 = s_seg[0][t - off];
-      g1 = s_seg[1][t - off];
-      g2 = s_seg[2][t - off];
-    }
-    __syncthreads();
-    s_scan[0][t] += a0;
-    s_scan[1][t] += a1;
-    s_scan[2][t] += a2;
-    s_seg[0][t] += g0;
-    s_seg[1][t] += g1;
-    s_seg[2][t] = max(s_seg[2][t], g2);
-    __syncthreads();
+  if (lane == 63) {
+    int* w = s_wave + wave * 8;
+    w[0] = nu_i;
+    w[1] = ns_i;
+    w[2] = np_i;
+    w[3] = nw_i;
+    w[4] = pm;
   }
-  // segment starts: segment x holds (its most pieces) x (its split rows)
-  // piece-major units, then its other rows
+  __syncthreads();
+  int ub = nu_i - nu, sb = ns_i - ns, pb = np_i - np;
+  for (int w = 0; w < wave; ++w) {
+    ub += s_wave[w * 8];
+    sb += s_wave[w * 8 + 1];
+    pb += s_wave[w * 8 + 2];
+  }
+  const int w0 = wave & ~1;  // the segment's first wave
+  const int n_split = s_wave[w0 * 8 + 2] + s_wave[w0 * 8 + 10], n_whole = s_wave[w0 * 8 + 3] + s_wave[w0 * 8 + 11];
+  const int p_most = max(s_wave[w0 * 8 + 4], s_wave[w0 * 8 + 12]);
+  const int ks0 = np_i - np + (wave & 1 ? s_wave[w0 * 8 + 2] : 0);
+  const int kw0 = nw_i - nw + (wave & 1 ? s_wave[w0 * 8 + 3] : 0);
   if (t == 0) {
+    // segment starts: segment x holds (its most pieces) x (its split rows)
+    // piece-major units, then its other rows
     int b = 0;
     for (int x = 0; x < 8; ++x) {
+      const int* w = s_wave + x * 16;
       s_base[x] = b;
-      const int last = x * 128 + 127;
-      b += segmented ? s_seg[2][last] * s_seg[0][last] + s_seg[1][last] : 0;
+      if (segmented) b += max(w[4], w[12]) * (w[2] + w[10]) + w[3] + w[11];
     }
     s_base[8] = b;
   }
-  __syncthreads();
-  int sb = s_scan[1][t] - ns, pb = s_scan[2][t] - np;
   if (segmented) {
-    const int x = t >> 7, last = x * 128 + 127;
-    const int n_split = s_seg[0][last], p_most = s_seg[2][last];
-    const int base = s_base[x];
-    const int n_whole = s_seg[1][last];
+    const int x = t >> 7;
     const int keep = n_whole - n_whole / kTailDiv;  // whole rows of rank >= keep form the tail
     // the tail's order: rows per length bucket, then each bucket's first slot
     // counted from the longest bucket down
-    for (int i = t; i < 8 * kTailBins; i += 1024) s_tail[i / kTailBins][i % kTailBins] = 0;
+    for (int i = t; i < kPlanTailInts; i += kPrepThreads) s_tail[i] = 0;
     __syncthreads();
+    const int base = s_base[x];
     {
-      int kw = s_seg[1][t] - nw;
+      int kw = kw0;
       for (int k = k0; k < k1; ++k) {
         const int c = len_of(row_at(k));
         if (c < 0 || c > L) continue;
-        if (kw >= keep) atomicAdd(&s_tail[x][tail_bin(c, L)], 1);
+        if (kw >= keep) atomicAdd(&s_tail[x * kTailBins + tail_bin(c, L)], 1);
         ++kw;
       }
     }
     __syncthreads();
-    if (t < 8) {
-      int run = 0;
-      for (int b = kTailBins - 1; b >= 0; --b) {
-        const int n = s_tail[t][b];
-        s_tail[t][b] = run;
-        run += n;
-      }
+    // wave x < 8 turns segment x's buckets into slots, four buckets a lane
+    if (wave < 8) {
+      static_assert(kTailBins == 256, "four buckets a lane");
+      int* bin = s_tail + wave * kTailBins + kTailBins - 4 - 4 * lane;  // lane 0 the longest rows
+      const int b3 = bin[3], b2 = bin[2], b1 = bin[1], b0 = bin[0];
+      const int sum = b3 + b2 + b1 + b0;
+      const int run = wave_scan(sum, lane) - sum;
+      bin[3] = run;
+      bin[2] = run + b3;
+      bin[1] = run + b3 + b2;
+      bin[0] = run + b3 + b2 + b1;
     }
     __syncthreads();
-    int ks = s_seg[0][t] - np, kw = s_seg[1][t] - nw;  // ranks of this thread's first rows
+    int ks = ks0, kw = kw0;  // ranks of this thread's first rows
     for (int k = k0; k < k1; ++k) {
       const int r = row_at(k);
       const int c = len_of(r);
       if (c < 0) continue;
       const int pieces = c > L ? (c + L - 1) / L : 1;
       if (pieces == 1) {
-        const int rank = kw < keep ? kw : keep + atomicAdd(&s_tail[x][tail_bin(c, L)], 1);
+        const int rank = kw < keep ? kw : keep + atomicAdd(&s_tail[x * kTailBins + tail_bin(c, L)], 1);
         const int pos = base + p_most * n_split + rank;
-        if (pos < units_cap) units[pos] = make_int4(r, 0, c, -1);
+        if (pos < a.units_cap) a.units[pos] = make_int4(r, 0, c, -1);
         ++kw;
         continue;
       }
-      const bool fits = sb + pieces <= slots_cap && pb < splits_cap;  // always, by the bounds above
+      const bool fits = sb + pieces <= a.slots_cap && pb < a.splits_cap;  // always, by the bounds above
       for (int s = 0; s < p_most; ++s) {
         int4 un = make_int4(-1, 0, 0, -1);
         if (s < pieces && fits)
           un = make_int4(r, c * s / pieces, c * (s + 1) / pieces, sb + s);  // c s < 2^24: 32-bit
         const int pos = base + s * n_split + ks;
-        if (pos < units_cap) units[pos] = un;
+        if (pos < a.units_cap) a.units[pos] = un;
       }
-      if (fits) splits[pb] = make_int4(r, sb, pieces, 0);
+      if (fits) a.splits[pb] = make_int4(r, sb, pieces, 0);
       ++ks;
       sb += pieces;
       ++pb;
     }
-    if (t == 1023) {
-      hdr[0] = min(s_base[8], units_cap);
-      hdr[1] = min(s_scan[2][1023], splits_cap);
-      hdr[2] = L;
-      hdr[3] = 0;
-      for (int i = 0; i < 9; ++i) hdr[4 + i] = min(s_base[i], units_cap);
+  } else {
+    for (int k = k0; k < k1; ++k) {
+      const int r = row_at(k);
+      const int c = len_of(r);
+      if (c < 0) continue;
+      const int pieces = c > L ? (c + L - 1) / L : 1;
+      // (past a capacity -- impossible by the bounds above -- the row stays one
+      // unit and its other entries become placeholders the kernel skips)
+      const bool split = pieces > 1 && sb + pieces <= a.slots_cap && pb < a.splits_cap;
+      for (int s = 0; s < pieces; ++s) {
+        const int b0 = c * s / pieces, b1 = c * (s + 1) / pieces;  // c s < 2^24: 32-bit
+        int4 un = make_int4(r, b0, b1, split ? sb + s : -1);
+        if (!split && pieces > 1) un = s == 0 ? make_int4(r, 0, c, -1) : make_int4(-1, 0, 0, -1);
+        if (ub + s < a.units_cap) a.units[ub + s] = un;
+      }
+      if (split) a.splits[pb] = make_int4(r, sb, pieces, 0);
+      ub += pieces;
+      if (pieces > 1) {
+        sb += pieces;
+        ++pb;
+      }
     }
+  }
+  if (t == kPrepThreads - 1) {
+    // (the last thread's running values are the totals)
+    const int n_units = segmented ? s_base[8] : ub;
+    a.hdr[0] = min(n_units, a.units_cap);
+    a.hdr[1] = min(pb, a.splits_cap);
+    a.hdr[2] = L;
+    a.hdr[3] = 0;
+    if (segmented)
+      for (int i = 0; i < 9; ++i) a.hdr[4 + i] = min(s_base[i], a.units_cap);
+  }
+}
+
+// ------------------------------------------------------------ pre-pass of a call
+// One launch before the attention kernel: its first workgroup plans the work
+// units and zeroes the queue counters (vector stores, so that a captured graph
+// replays it), the others rewrite K and, where the call multiplies it, V in
+// tile-major order.  Each takes one position range of kPrepTok<D> tokens of one
+// (batch, head):
+//   kt[bh][p][:] = k[bh][perm[p]][:], 0 at a padding position;
+//   vt[bh][b][d][j] = v[bh][perm[p]][d] for p = 128 b + j, transposed through LDS,
+//   so that key block b of a head is one contiguous D x 128 tile, key fastest.
+// A thread moves one 16-byte chunk of each, both loads in flight together.  The
+// rewrite is bound by memory (3.1 GB read and written at 75,600 tokens x 40 heads
+// x 128), and the plan, one workgroup's chain of scans, runs beside it instead of
+// before the attention kernel.  A workgroup takes its positions for several
+// pairs in turn, the next pair's loads requested before the current one's tile
+// is transposed: one pair a workgroup left the memory idle while sixteen waves
+// ended and sixteen began (0.63 ms there).  The raw K and V are read once, with
+// non-temporal loads, which leaves the caches to the copies the attention kernel
+// reads (0.585 -> 0.558 ms).
+// Measured, three launches (K, V, plan) -> one: 0.60 -> 0.56 ms there, 93 -> 61 us
+// at 32,760 tokens x 12 heads, 13 -> 4 us at 957 tokens x 2 heads.
+template <int D>
+constexpr int kPrepTok = kPrepThreads / (D / 8);
+
+template <int D, bool WITH_V>
+__global__ __launch_bounds__(kPrepThreads) void prep_kernel(const uint4* __restrict__ k, uint4* __restrict__ kt,
+                                                            const uint4* __restrict__ v, uint16_t* __restrict__ vt,
+                                                            const int32_t* __restrict__ perm, int N, int n_pad,
+                                                            int bhs, int pairs_per_wg, PlanArgs pa) {
+  extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+  const int t = threadIdx.x;
+  if (blockIdx.x == 0) {
+    if (t < kRowCounters) pa.ctr[t] = 0;
+    if (pa.cnt) plan_units(pa, lds);
     return;
   }
-  int ub = s_scan[0][t] - nu;
-  for (int k = k0; k < k1; ++k) {
-    const int r = row_at(k);
-    const int c = len_of(r);
-    if (c < 0) continue;
-    const int pieces = c > L ? (c + L - 1) / L : 1;
-    // (past a capacity -- impossible by the bounds above -- the row stays one
-    // unit and its other entries become placeholders the kernel skips)
-    const bool split = pieces > 1 && sb + pieces <= slots_cap && pb < splits_cap;
-    for (int s = 0; s < pieces; ++s) {
-      const int b0 = c * s / pieces, b1 = c * (s + 1) / pieces;  // c s < 2^24: 32-bit
-      int4 un = make_int4(r, b0, b1, split ? sb + s : -1);
-      if (!split && pieces > 1) un = s == 0 ? make_int4(r, 0, c, -1) : make_int4(-1, 0, 0, -1);
-      if (ub + s < units_cap) units[ub + s] = un;
+  constexpr int TOK = kPrepTok<D>, CH = D / 8, LS = D + 2;
+  const uint32_t per = (uint32_t)n_pad / TOK, b = blockIdx.x - 1;
+  const int bh0 = (int)(b / per) * pairs_per_wg, bh1 = min(bhs, bh0 + pairs_per_wg);
+  const int p0 = (int)(b % per) * TOK;
+  const int j = t / CH, c = t % CH;
+  const int tok = perm[p0 + j];
+  const uint4 zero = make_uint4(0, 0, 0, 0);
+  auto chunk = [&](const uint4* src, int bh) {
+    if (tok < 0) return zero;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const u32x4 x = __builtin_nontemporal_load((const u32x4*)(src + ((size_t)bh * N + tok) * CH + c));
+    return make_uint4(x[0], x[1], x[2], x[3]);
+  };
+  uint4 kx = chunk(k, bh0), vx = zero;
+  if (WITH_V) vx = chunk(v, bh0);
+  for (int bh = bh0; bh < bh1; ++bh) {
+    // (two tiles in turn, so that one barrier a pair keeps a tile's writes behind
+    // its last reads)
+    uint16_t* tile = (uint16_t*)lds + (WITH_V ? ((bh - bh0) & 1) * TOK * LS : 0);
+    if constexpr (WITH_V) {
+      // rows of D + 2 halves: 4-byte aligned, an odd number of words
+      uint32_t* dst = (uint32_t*)(tile + j * LS + c * 8);
+      dst[0] = vx.x;
+      dst[1] = vx.y;
+      dst[2] = vx.z;
+      dst[3] = vx.w;
     }
-    if (split) splits[pb] = make_int4(r, sb, pieces, 0);
-    ub += pieces;
-    if (pieces > 1) {
-      sb += pieces;
-      ++pb;
+    kt[((size_t)bh * n_pad + p0) * CH + t] = kx;
+    if (bh + 1 < bh1) {
+      kx = chunk(k, bh + 1);
+      if (WITH_V) vx = chunk(v, bh + 1);
     }
-  }
-  if (t == 1023) {
-    hdr[0] = min(s_scan[0][1023], units_cap);
-    hdr[1] = min(s_scan[2][1023], splits_cap);
-    hdr[2] = L;
-    hdr[3] = 0;
+    if constexpr (WITH_V) {
+      lds_barrier();  // (leaves the next pair's loads and the stores in flight)
+      const int d = t / (TOK / 8), tc = t % (TOK / 8);
+      uint32_t w[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        w[e] = (uint32_t)tile[(tc * 8 + 2 * e) * LS + d] | ((uint32_t)tile[(tc * 8 + 2 * e + 1) * LS + d] << 16);
+      const int p = p0 + tc * 8;
+      *(uint4*)(vt + (size_t)bh * n_pad * D + ((size_t)(p / kBK) * D + d) * kBK + p % kBK) =
+          make_uint4(w[0], w[1], w[2], w[3]);
+    }
   }
 }
 
@@ -1726,12 +1786,33 @@ int k64_sparse_grid_cap_d(const tra_plan_s& p) {
   return std::max(1, std::max(a, b)) * std::max(p.n_cu, 1);
 }
 
-// Work units of a block-sparse or token-level call for `grid` workgroups, and
-// the merge of its split rows.
-void launch_plan_units(const tra_plan_s& p, const AttnArgs& a, int grid, hipStream_t s) {
-  hipLaunchKernelGGL(plan_units_kernel, dim3(1), dim3(1024), 0, s, a.cnt, a.order, p.rows, p.NB, grid,
-                     (int4*)p.d_units, p.units_cap, (int4*)p.d_splits, p.splits_cap, p.slots_cap, p.d_unit_hdr,
-                     p.d_row_ctr);
+// Rows of at most kSplitMin blocks are never cut: a plan with no more blocks than
+// that needs neither work units nor the merge.
+bool has_units(const tra_plan_s& p, const AttnArgs& a) { return a.sparse && p.NB > kSplitMin; }
+
+// The pre-pass of a call whose attention kernel runs `grid` workgroups.
+template <int D>
+void launch_prep(const tra_plan_s& p, const AttnArgs& a, int grid, hipStream_t s) {
+  const bool units = has_units(p, a);
+  const PlanArgs pa{units ? a.cnt : nullptr, a.order, p.rows, p.NB, grid, p.units_cap, p.splits_cap, p.slots_cap,
+                    (int4*)p.d_units, (int4*)p.d_splits, p.d_unit_hdr, p.d_row_ctr};
+  // up to eight pairs a workgroup, as long as 16 workgroups a CU are left
+  const int bhs = p.cfg.batch * p.cfg.heads, per = p.n_pad / kPrepTok<D>;
+  const int ppw = (int)std::min<long long>(8, std::max<long long>(1, (long long)per * bhs / (16 * std::max(p.n_cu, 1))));
+  const unsigned blocks = (unsigned)per * (unsigned)((bhs + ppw - 1) / ppw) + 1;
+  const size_t tile = a.v ? 2 * (size_t)kPrepTok<D> * (D + 2) * sizeof(uint16_t) : 0;
+  const size_t lds = std::max(tile, units ? plan_lds_bytes(p.rows) : 0);
+  if (a.v)
+    hipLaunchKernelGGL((prep_kernel<D, true>), dim3(blocks), dim3(kPrepThreads), lds, s, (const uint4*)a.k,
+                       (uint4*)p.d_kt, (const uint4*)a.v, p.d_vt, p.d_perm, p.S, p.n_pad, bhs, ppw, pa);
+  else
+    hipLaunchKernelGGL((prep_kernel<D, false>), dim3(blocks), dim3(kPrepThreads), lds, s, (const uint4*)a.k,
+                       (uint4*)p.d_kt, (const uint4*)a.v, p.d_vt, p.d_perm, p.S, p.n_pad, bhs, ppw, pa);
+}
+
+// The unit table of a call, NULL where its rows are its work.
+const int4* unit_table(const tra_plan_s& p, const AttnArgs& a) {
+  return has_units(p, a) ? (const int4*)p.d_units : nullptr;
 }
 
 template <int D>
@@ -1750,20 +1831,15 @@ void launch_k64_lse(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
   const float scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)D));
   const size_t lds_bytes = SPARSE ? (size_t)p.NB * sizeof(int32_t) : 0;
   int grid = resident_grid(attn_k64_kernel<D, SPARSE, LSE>, lds_bytes, p);
-  if (SPARSE) {
-    grid = std::min(grid, p.split_wg_cap);
-    launch_plan_units(p, a, grid, s);
-  } else {
-    hipLaunchKernelGGL(reset_row_counters, dim3(1), dim3(kRowCounters), 0, s, p.d_row_ctr);
-  }
+  if (SPARSE) grid = std::min(grid, p.split_wg_cap);
+  launch_prep<D>(p, a, grid, s);
   if (a.ev_start) (void)hipEventRecord(a.ev_start, s);
   hipLaunchKernelGGL((attn_k64_kernel<D, SPARSE, LSE>), dim3(grid), dim3(kThreads), lds_bytes, s,
-                     (const uint16_t*)a.q, p.d_kt, p.d_vt, (uint16_t*)a.o, a.lse, p.d_perm, a.cols,
-                     p.cfg.block_layout == TRA_BLOCKS_TILES ? p.d_bcount : nullptr, (const int4*)p.d_units,
-                     p.d_unit_hdr, a.order != nullptr, p.S, p.n_pad, p.NB, p.rows, scale_log2, p.d_row_ctr,
-                     p.d_part, p.d_pstats);
+                     (const uint16_t*)a.q, p.d_kt, p.d_vt, (uint16_t*)a.o, a.lse, p.d_perm, a.cnt, a.cols, a.order,
+                     p.cfg.block_layout == TRA_BLOCKS_TILES ? p.d_bcount : nullptr, unit_table(p, a), p.d_unit_hdr,
+                     p.S, p.n_pad, p.NB, p.rows, scale_log2, p.d_row_ctr, p.d_part, p.d_pstats);
   if (a.ev_stop) (void)hipEventRecord(a.ev_stop, s);
-  if (SPARSE) launch_merge<D>(p, a, s);
+  if (has_units(p, a)) launch_merge<D>(p, a, s);
 }
 
 template <int D, bool SPARSE>
@@ -2008,7 +2084,7 @@ template <int D>
 void launch_fused_entropy_output(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
   const float scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)D));
   const int grid = resident_grid(attn_fused_kernel<D>, 0, p, kFusedThreads);
-  hipLaunchKernelGGL(reset_row_counters, dim3(1), dim3(kRowCounters), 0, s, p.d_row_ctr);
+  launch_prep<D>(p, a, grid, s);
   if (a.ev_start) (void)hipEventRecord(a.ev_start, s);
   hipLaunchKernelGGL((attn_fused_kernel<D>), dim3(grid), dim3(kFusedThreads), 0, s, (const uint16_t*)a.q,
                      p.d_kt, p.d_vt, (uint16_t*)a.o, a.entropy, p.d_perm, p.S, p.n_pad, p.NB, p.rows,
@@ -2024,35 +2100,19 @@ void launch_variant(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
   const TokArgs tk{a.radius_sq, p.cfg.distance == TRA_DIST_1D ? p.d_thr1 : p.d_thr, p.d_kinfo, p.d_blocks,
                    p.d_coord, p.d_kfeat, p.N, p.cfg.frames, p.n_cap};
   int grid = resident_grid(attn_bf16_kernel<D, SPARSE, PV, ENT, 2, TOK>, lds_bytes, p);
-  if (SPARSE) {
-    grid = std::min(grid, p.split_wg_cap);
-    launch_plan_units(p, a, grid, s);
-  } else {
-    hipLaunchKernelGGL(reset_row_counters, dim3(1), dim3(kRowCounters), 0, s, p.d_row_ctr);
-  }
+  if (SPARSE) grid = std::min(grid, p.split_wg_cap);
+  launch_prep<D>(p, a, grid, s);
   if (a.ev_start) (void)hipEventRecord(a.ev_start, s);
   hipLaunchKernelGGL((attn_bf16_kernel<D, SPARSE, PV, ENT, 2, TOK>), dim3(grid), dim3(kThreads), lds_bytes, s,
-                     (const uint16_t*)a.q, p.d_kt, p.d_vt, (uint16_t*)a.o, a.lse, a.entropy, p.d_perm, a.cols,
-                     (const int4*)p.d_units, p.d_unit_hdr, a.order != nullptr, p.S, p.n_pad, p.NB, p.rows,
-                     scale_log2, tk, p.d_row_ctr, p.d_part, p.d_pstats);
+                     (const uint16_t*)a.q, p.d_kt, p.d_vt, (uint16_t*)a.o, a.lse, a.entropy, p.d_perm, a.cnt,
+                     a.cols, a.order, unit_table(p, a), p.d_unit_hdr, p.S, p.n_pad, p.NB, p.rows, scale_log2, tk,
+                     p.d_row_ctr, p.d_part, p.d_pstats);
   if (a.ev_stop) (void)hipEventRecord(a.ev_stop, s);
-  if (SPARSE) launch_merge<D>(p, a, s);
+  if (has_units(p, a)) launch_merge<D>(p, a, s);
 }
 
 template <int D>
 hipError_t launch_bf16_d(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
-  const int bhs = p.cfg.batch * p.cfg.heads;
-  const unsigned gy = (unsigned)std::min(bhs, kGatherMaxY);
-  hipLaunchKernelGGL((gather_k_kernel<D>), dim3((unsigned)((p.n_pad * (D / 8) + 255) / 256), gy), dim3(256), 0, s,
-                     (const uint4*)a.k, (uint4*)p.d_kt, p.d_perm, p.S, p.n_pad, bhs);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (a.v) {
-    hipLaunchKernelGGL((gather_vt_kernel<D>), dim3(p.n_pad / 64, gy), dim3(256), 0, s,
-                       (const uint16_t*)a.v, p.d_vt, p.d_perm, p.S, p.n_pad, bhs);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
   const bool text = p.S > p.N;
   if (a.sparse && a.radius_sq && p.cfg.distance == TRA_DIST_1D && text) launch_variant<D, true, true, false, 6>(p, a, s);
   else if (a.sparse && a.radius_sq && p.cfg.distance == TRA_DIST_1D) launch_variant<D, true, true, false, 2>(p, a, s);

@@ -1,0 +1,30 @@
+"""The bf16 calls' pre-pass where one workgroup rewrites several heads' keys and
+values in turn and the last one has fewer: every head of a many-head plan bit
+for bit equal to a one-head plan's call (one head a workgroup)."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("heads,head_dim", [(17, 128), (33, 64)])
+def test_heads_in_turn_equal_one_head(heads, head_dim):
+    import torch
+    import paper_2608_02504_amd as tra
+    cfg = dict(frames=9, height=45, width=80, head_dim=head_dim)   # 32,400 tokens, a ragged last block
+    plan, one = tra.Plan(tra.Config(1, heads, **cfg)), tra.Plan(tra.Config(1, 1, **cfg))
+    S, NB = plan.n_tokens, plan.n_blocks
+    # two heads a workgroup at least (256 CUs, 64 tokens of 128 components a workgroup)
+    assert (NB * 2 * head_dim // 128) * heads // (16 * 256) >= 2 and heads % 2
+    g = torch.Generator(device="cuda").manual_seed(3)
+    q, k, v = (torch.randn(1, heads, S, head_dim, generator=g, device="cuda").bfloat16() for _ in range(3))
+    u = torch.arange(NB, device="cuda")
+    pair = torch.stack([u, (7 * u + 3) % NB], 1).sort(1).values
+    pair = torch.where((pair[:, :1] == pair[:, 1:]) & (torch.arange(2, device="cuda") == 1), -1, pair)
+    cols = torch.full((1, heads, NB, NB), -1, dtype=torch.int32, device="cuda")
+    cols[..., :2] = pair.int()
+    cnt = (pair >= 0).sum(1).int().expand(1, heads, NB).contiguous()
+    o, o1 = torch.empty_like(q), torch.empty_like(q[:, :1])
+    tra.tra_sparse_attention(plan, q, k, v, cnt, cols, None, o)
+    for h in range(heads):
+        tra.tra_sparse_attention(one, *(t[:, h:h + 1].contiguous() for t in (q, k, v, cnt, cols)), None, o1)
+        assert torch.equal(o[:, h:h + 1], o1), h
