@@ -309,8 +309,9 @@ tra_status tra_build_block_mask_noalloc(tra_plan plan, const int32_t* radius_sq,
  * retained keys, or NULL.  A row with cnt = 0 gets o = 0, lse = -inf.
  * Work is balanced by cutting long lists: with T the total of the (clamped)
  * list lengths of the rows computed and G the number of workgroups the GPU
- * holds at once, a row of more than L = max(48, ceil(T / 16G)) entries
- * is computed as ceil(cnt / L) pieces of consecutive entries whose partial
+ * holds at once, a row of more than L entries, L one of 1, 4/3, 2, 8/3 and 4
+ * times max(48, ceil(T / 16G)) chosen from the row lengths alone (the least
+ * 8 * pieces / G + longest unit / 4), is computed as ceil(cnt / L) pieces of consecutive entries whose partial
  * softmax states are merged afterwards, so its result differs from an
  * unsplit computation by rounding only (each piece rounds its probabilities
  * to bf16 relative to its own running maximum); rows of at most 48 entries

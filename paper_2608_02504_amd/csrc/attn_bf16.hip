@@ -1341,12 +1341,27 @@ __global__ __launch_bounds__(kThreads, 3) void attn_k64_kernel(
   }
 }
 
+// Length L of a piece.  A piece costs its partial result (67 KB written and read
+// back at head_dim 128) and a unit's fixed time, about kPieceCost list entries of
+// one workgroup's time; the call ends, on average, about a quarter of its longest
+// unit after its workgroups would if their work were even.  Of five lengths from
+// max(kSplitMin, ceil(T / (G kSplitPerWG))) to four times that, the one with the
+// least pieces * kPieceCost / G + longest unit / 4 is taken.  Always the first would
+// cut nearly every row in two where most are a little longer than it: 33 x 45 x 80
+// + 256 text tokens x 3 heads at 9 % of the block pairs, rows of 40 to 78 entries
+// for 768 workgroups, 2.17 ms at L = 48 (0.22 of it the merge) and 1.98 at L = 96.
+constexpr int kSplitCands = 5;
+constexpr int kPieceCost = 8;
+__device__ __forceinline__ int split_cand(int L, int i) {
+  return i == 0 ? L : i == 1 ? L * 4 / 3 : i == 2 ? L * 2 : i == 3 ? L * 8 / 3 : L * 4;
+}
+
 // Work units of a block-sparse or token-level call (one workgroup of 1024
 // threads).  (The token call on whole rows ended on its longest ones: 30 x 52 x
 // 21 frames, 12 heads at 15 % of the block pairs, 21 of 3,072 rows keeping all
 // 256 blocks, took 2.00 ms, on units 1.23 ms.)  With T
-// the total list length and G the attention grid, L = max(kSplitMin, ceil(T /
-// (G kSplitPerWG))) (doubled while the pieces would exceed the workspace's
+// the total list length and G the attention grid, L the piece length above
+// (doubled while the pieces would exceed the workspace's
 // partial slots, which its capacity, 2 G kSplitPerWG + 1 slots, rules out),
 // and a row of c > L entries becomes ceil(c / L) units of near-equal
 // length, each writing a partial slot, so that no unit holds more than about
@@ -1462,11 +1477,44 @@ __device__ void plan_units(const PlanArgs& a, uint8_t* lds) {
     for (int w = 0; w < kPrepWaves; ++w) x += ((const long long*)s_wave)[w];
     return x;
   };
+  auto block_max = [&](int x) {
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) x = max(x, __shfl_xor(x, o));
+    __syncthreads();
+    if (lane == 0) s_wave[wave] = x;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kPrepWaves; ++w) x = max(x, s_wave[w]);
+    return x;
+  };
   long long tot = 0;
   for (int k = k0; k < k1; ++k) tot += max(len_of(row_at(k)), 0);
   const long long total = block_sum(tot);
   const long long share = (long long)max(a.n_wg, 1) * kSplitPerWG;
   int L = (int)max((long long)kSplitMin, (total + share - 1) / share);
+  {
+    // pieces and longest unit under each candidate length, then the cheapest
+    int n_c[kSplitCands] = {0}, len_c[kSplitCands] = {0};
+    for (int k = k0; k < k1; ++k) {
+      const int c = len_of(row_at(k));
+#pragma unroll
+      for (int i = 0; i < kSplitCands; ++i) {
+        const int Lc = split_cand(L, i), pieces = c > Lc ? (c + Lc - 1) / Lc : 1;
+        n_c[i] += pieces > 1 ? pieces : 0;
+        len_c[i] = max(len_c[i], (c + pieces - 1) / pieces);
+      }
+    }
+    const int L0 = L;
+    long long best = LLONG_MAX;
+#pragma unroll
+    for (int i = 0; i < kSplitCands; ++i) {
+      const long long cost = block_sum(n_c[i]) * (4 * kPieceCost) + (long long)a.n_wg * block_max(len_c[i]);
+      if (cost < best) {
+        best = cost;
+        L = split_cand(L0, i);
+      }
+    }
+  }
   // per thread: units, slots and split rows of its positions; L doubles until
   // the pieces of the split rows fit the partial slots
   int nu, ns, np, nw, pmx;
@@ -1703,8 +1751,15 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const uint4* __restr
 // Merges the pieces of the split rows: m = max over pieces of m_p (pieces
 // with no weight skipped), w_p = 2^(m_p - m), o = sum_p w_p O_p / sum_p w_p lr_p
 // (the rounded sums the pieces' bf16 weights add up to), lse = ln 2 (m +
-// log2 sum_p w_p l_p).  One workgroup per split row at a time; thread t takes
-// query t / 2 and half t % 2 of its D outputs.
+// log2 sum_p w_p l_p).  A thread takes four components of one query, a workgroup
+// 1024 / D queries of a split row, one after another over the pieces with eight
+// pieces' loads in flight: what bounds it is the chain of those loads where few rows
+// are split and the bytes (68 KB a piece) where many are.  One workgroup per whole
+// row left most of the chip idle in the first case (21 x 30 x 52 x 12 heads, 21
+// rows of 6 pieces and some of 2: 33 -> 19 us; 555 rows of 4 pieces: 59 and 60).
+template <int D>
+constexpr int kMergeQueries = 256 / (D / 4);
+
 template <int D, bool LSE>
 __global__ __launch_bounds__(256) void merge_split_rows_kernel(const int4* __restrict__ splits,
                                                                const int32_t* __restrict__ hdr,
@@ -1712,65 +1767,58 @@ __global__ __launch_bounds__(256) void merge_split_rows_kernel(const int4* __res
                                                                const float* __restrict__ pstats,
                                                                uint16_t* __restrict__ o, float* __restrict__ lse,
                                                                const int32_t* __restrict__ perm, int N, int NB) {
-  constexpr int HD = D / 2;
-  const int n_split = hdr[1];
-  const int t = threadIdx.x, qi = t >> 1, hd = t & 1;
-  for (int sp = blockIdx.x; sp < n_split; sp += gridDim.x) {
-    const int4 e = splits[sp];
+  constexpr int LPQ = D / 4, CHUNKS = kBQ / kMergeQueries<D>;
+  const int n_work = hdr[1] * CHUNKS;
+  const int t = threadIdx.x, c4 = t % LPQ;
+  for (int i = blockIdx.x; i < n_work; i += gridDim.x) {
+    const int4 e = splits[i / CHUNKS];
     const int r = e.x, slot0 = e.y, pieces = e.z;
     const int bh = r / NB, u = r - bh * NB;
+    const int qi = (i % CHUNKS) * kMergeQueries<D> + t / LPQ;
     const int qtok = perm[u * kBQ + qi];  // -1 at a padding position
     if (qtok < 0) continue;
+    const float* ps0 = pstats + (size_t)slot0 * 3 * kBQ + qi;
+    const float* po0 = part + ((size_t)slot0 * kBQ + qi) * D + 4 * c4;
     float m = -INFINITY;
-#pragma unroll 4
+#pragma unroll 8
     for (int p = 0; p < pieces; ++p) {
-      const float* ps = pstats + (size_t)(slot0 + p) * 3 * kBQ;
-      if (ps[kBQ + qi] > 0.f) m = fmaxf(m, ps[qi]);
+      const float* ps = ps0 + (size_t)p * 3 * kBQ;
+      m = ps[kBQ] > 0.f ? fmaxf(m, ps[0]) : m;
     }
-    float acc[HD];
-#pragma unroll
-    for (int j = 0; j < HD; ++j) acc[j] = 0.f;
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     float lr = 0.f, lf = 0.f;
-#pragma unroll 2  // two pieces' loads in flight
+#pragma unroll 8
     for (int p = 0; p < pieces; ++p) {
-      const float* ps = pstats + (size_t)(slot0 + p) * 3 * kBQ;
-      const float lrp = ps[kBQ + qi];
-      if (!(lrp > 0.f)) continue;
-      const float w = __builtin_amdgcn_exp2f(ps[qi] - m);
-      lr += w * lrp;
-      if (LSE) lf += w * ps[2 * kBQ + qi];
-      const float4* src = (const float4*)(part + ((size_t)(slot0 + p) * kBQ + qi) * D + hd * HD);
-#pragma unroll
-      for (int j = 0; j < HD / 4; ++j) {
-        const float4 x = src[j];
-        acc[4 * j] += w * x.x;
-        acc[4 * j + 1] += w * x.y;
-        acc[4 * j + 2] += w * x.z;
-        acc[4 * j + 3] += w * x.w;
-      }
+      const float* ps = ps0 + (size_t)p * 3 * kBQ;
+      const float4 x = *(const float4*)(po0 + (size_t)p * kBQ * D);
+      const float lrp = ps[kBQ];
+      const bool used = lrp > 0.f;  // (a piece with no weight adds nothing, whatever its sums hold)
+      const float w = used ? __builtin_amdgcn_exp2f(ps[0] - m) : 0.f;
+      lr += used ? w * lrp : 0.f;
+      if (LSE) lf += used ? w * ps[2 * kBQ] : 0.f;
+      acc.x += used ? w * x.x : 0.f;
+      acc.y += used ? w * x.y : 0.f;
+      acc.z += used ? w * x.z : 0.f;
+      acc.w += used ? w * x.w : 0.f;
     }
     const size_t tok = (size_t)bh * N + qtok;
     const float inv = lr > 0.f ? 1.f / lr : 0.f;
-    uint2* dst = (uint2*)(o + tok * D + hd * HD);
-#pragma unroll
-    for (int j = 0; j < HD / 4; ++j) {
-      uint2 w2;
-      w2.x = pack_bf16x2(acc[4 * j] * inv, acc[4 * j + 1] * inv);
-      w2.y = pack_bf16x2(acc[4 * j + 2] * inv, acc[4 * j + 3] * inv);
-      dst[j] = w2;
-    }
-    if (LSE && hd == 0) lse[tok] = lf > 0.f ? 0.69314718055994531f * (m + __log2f(lf)) : -INFINITY;
+    uint2 w2;
+    w2.x = pack_bf16x2(acc.x * inv, acc.y * inv);
+    w2.y = pack_bf16x2(acc.z * inv, acc.w * inv);
+    *(uint2*)(o + tok * D + 4 * c4) = w2;
+    if (LSE && c4 == 0) lse[tok] = lf > 0.f ? 0.69314718055994531f * (m + __log2f(lf)) : -INFINITY;
   }
 }
 
 // Grid of a persistent attention kernel: as many workgroups as can be resident
-// at once (the occupancy its registers and LDS allow), capped by the row count.
+// at once (the occupancy its registers and LDS allow), at most `work`.
 template <typename K>
-int resident_grid(K kernel, size_t lds_bytes, const tra_plan_s& p, int threads = kThreads) {
+int resident_grid(K kernel, size_t lds_bytes, const tra_plan_s& p, long long work, int threads = kThreads) {
   int per_cu = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, lds_bytes) != hipSuccess || per_cu < 1)
     per_cu = 1;
-  return std::min(p.rows, per_cu * std::max(p.n_cu, 1));
+  return (int)std::min<long long>(work, per_cu * std::max(p.n_cu, 1));
 }
 
 template <int D>
@@ -1790,7 +1838,14 @@ int k64_sparse_grid_cap_d(const tra_plan_s& p) {
 // that needs neither work units nor the merge.
 bool has_units(const tra_plan_s& p, const AttnArgs& a) { return a.sparse && p.NB > kSplitMin; }
 
-// The pre-pass of a call whose attention kernel runs `grid` workgroups.
+// At most how many work items a call has: its rows, each cut into the most pieces
+// a list of NB entries can be.  (A grid of as many workgroups as rows would leave
+// the pieces of few long rows to few workgroups.)
+long long most_work(const tra_plan_s& p, const AttnArgs& a) {
+  return (long long)p.rows * (has_units(p, a) ? (p.NB + kSplitMin - 1) / kSplitMin : 1);
+}
+
+// The pre-pass of a call whose work is cut for `grid` workgroups.
 template <int D>
 void launch_prep(const tra_plan_s& p, const AttnArgs& a, int grid, hipStream_t s) {
   const bool units = has_units(p, a);
@@ -1817,7 +1872,7 @@ const int4* unit_table(const tra_plan_s& p, const AttnArgs& a) {
 
 template <int D>
 void launch_merge(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
-  const dim3 grid(std::max(1, std::min(p.splits_cap, 1024)));
+  const dim3 grid(std::max(1, (int)std::min<long long>((long long)p.splits_cap * (kBQ / kMergeQueries<D>), 16LL * p.n_cu)));
   if (a.lse)
     hipLaunchKernelGGL((merge_split_rows_kernel<D, true>), grid, dim3(256), 0, s, (const int4*)p.d_splits,
                        p.d_unit_hdr, p.d_part, p.d_pstats, (uint16_t*)a.o, a.lse, p.d_perm, p.S, p.NB);
@@ -1830,9 +1885,10 @@ template <int D, bool SPARSE, bool LSE>
 void launch_k64_lse(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
   const float scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)D));
   const size_t lds_bytes = SPARSE ? (size_t)p.NB * sizeof(int32_t) : 0;
-  int grid = resident_grid(attn_k64_kernel<D, SPARSE, LSE>, lds_bytes, p);
-  if (SPARSE) grid = std::min(grid, p.split_wg_cap);
-  launch_prep<D>(p, a, grid, s);
+  const int cap = std::min(resident_grid(attn_k64_kernel<D, SPARSE, LSE>, lds_bytes, p, INT_MAX),
+                           SPARSE ? p.split_wg_cap : INT_MAX);
+  const int grid = (int)std::min<long long>(cap, most_work(p, a));
+  launch_prep<D>(p, a, cap, s);
   if (a.ev_start) (void)hipEventRecord(a.ev_start, s);
   hipLaunchKernelGGL((attn_k64_kernel<D, SPARSE, LSE>), dim3(grid), dim3(kThreads), lds_bytes, s,
                      (const uint16_t*)a.q, p.d_kt, p.d_vt, (uint16_t*)a.o, a.lse, p.d_perm, a.cnt, a.cols, a.order,
@@ -2083,7 +2139,7 @@ __global__ __launch_bounds__(kFusedThreads, 1) void attn_fused_kernel(
 template <int D>
 void launch_fused_entropy_output(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
   const float scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)D));
-  const int grid = resident_grid(attn_fused_kernel<D>, 0, p, kFusedThreads);
+  const int grid = resident_grid(attn_fused_kernel<D>, 0, p, p.rows, kFusedThreads);
   launch_prep<D>(p, a, grid, s);
   if (a.ev_start) (void)hipEventRecord(a.ev_start, s);
   hipLaunchKernelGGL((attn_fused_kernel<D>), dim3(grid), dim3(kFusedThreads), 0, s, (const uint16_t*)a.q,
@@ -2099,9 +2155,10 @@ void launch_variant(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
   if (TOK != 0) lds_bytes += (size_t)kBQ * p.cfg.frames * sizeof(uint16_t);
   const TokArgs tk{a.radius_sq, p.cfg.distance == TRA_DIST_1D ? p.d_thr1 : p.d_thr, p.d_kinfo, p.d_blocks,
                    p.d_coord, p.d_kfeat, p.N, p.cfg.frames, p.n_cap};
-  int grid = resident_grid(attn_bf16_kernel<D, SPARSE, PV, ENT, 2, TOK>, lds_bytes, p);
-  if (SPARSE) grid = std::min(grid, p.split_wg_cap);
-  launch_prep<D>(p, a, grid, s);
+  const int cap = std::min(resident_grid(attn_bf16_kernel<D, SPARSE, PV, ENT, 2, TOK>, lds_bytes, p, INT_MAX),
+                           SPARSE ? p.split_wg_cap : INT_MAX);
+  const int grid = (int)std::min<long long>(cap, most_work(p, a));
+  launch_prep<D>(p, a, cap, s);
   if (a.ev_start) (void)hipEventRecord(a.ev_start, s);
   hipLaunchKernelGGL((attn_bf16_kernel<D, SPARSE, PV, ENT, 2, TOK>), dim3(grid), dim3(kThreads), lds_bytes, s,
                      (const uint16_t*)a.q, p.d_kt, p.d_vt, (uint16_t*)a.o, a.lse, a.entropy, p.d_perm, a.cnt,

@@ -28,3 +28,26 @@ def test_heads_in_turn_equal_one_head(heads, head_dim):
     for h in range(heads):
         tra.tra_sparse_attention(one, *(t[:, h:h + 1].contiguous() for t in (q, k, v, cnt, cols)), None, o1)
         assert torch.equal(o[:, h:h + 1], o1), h
+
+
+@pytest.mark.parametrize("heads,whole", [(2, False), (8, True)])
+def test_piece_length_follows_the_rows(heads, whole):
+    """Rows of 61 blocks, every block kept: 122 of them are cut in two (the
+    pieces cost less than the longer tail), 488 are not (cutting them all would
+    cost more than it evens out) and equal the dense call bit for bit."""
+    import torch
+    import paper_2608_02504_amd as tra
+    plan = tra.Plan(tra.Config(1, heads, 5, 30, 52, 128))
+    S, NB = plan.n_tokens, plan.n_blocks
+    g = torch.Generator(device="cuda").manual_seed(4)
+    q, k, v = (torch.randn(1, heads, S, 128, generator=g, device="cuda").bfloat16() for _ in range(3))
+    cnt = torch.full((1, heads, NB), NB, dtype=torch.int32, device="cuda")
+    cols = torch.arange(NB, dtype=torch.int32, device="cuda").expand(1, heads, NB, NB).contiguous()
+    o, d = torch.empty_like(q), torch.empty_like(q)
+    lse, lse_d = (torch.empty(1, heads, S, device="cuda") for _ in range(2))
+    tra.tra_sparse_attention(plan, q, k, v, cnt, cols, None, o, lse)
+    tra.tra_dense_attention(plan, q, k, v, d, lse_d)
+    assert torch.equal(o, d) == whole
+    # bf16 outputs of the same sums: an ulp or two of values below 1
+    assert (o.float() - d.float()).abs().max() <= 2 ** -7
+    assert (lse - lse_d).abs().max() <= 1e-5 * lse_d.abs().max()
