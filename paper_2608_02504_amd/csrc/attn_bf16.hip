@@ -1,13 +1,15 @@
 // bf16 attention family on gfx950 matrix cores: dense attention (Eq. 1),
 // block-sparse TRA attention (Eq. 16 at block granularity), its token-level
 // form (the token mask of Eq. 15 inside the retained blocks) and the
-// online-softmax entropy pass (App. C.2, Alg. 2).  Three kernels:
+// online-softmax entropy pass (App. C.2, Alg. 2).  Four kernels:
 //   attn_k64_kernel   dense and block-sparse output, 64-key tiles, three
 //                     4-wave workgroups per CU;
 //   attn_bf16_kernel  token-level output (two 4-wave workgroups per CU) and the
 //                     entropy pass (four), 128-key tiles;
 //   attn_fused_kernel the entropy pass fused with the dense output, 8 waves
-//                     splitting the keys of one query block.
+//                     splitting the keys of one query block;
+//   attn_small_kernel all but the token-level output where rows are few, 8 waves
+//                     splitting the keys of 32 queries.
 //
 // Layout pre-pass
 //   K and V are first rewritten in tile-major order (Sec. 3.3: tokens of a
@@ -67,6 +69,8 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 constexpr int kBQ = 128;       // queries per workgroup (= block size)
 constexpr int kBK = 128;       // keys per tile (= block size)
 constexpr int kThreads = 256;
+// attn_small_kernel: waves and queries of a workgroup
+constexpr int kSmallWaves = 8, kSmallThreads = 64 * kSmallWaves, kSmallQ = 32;
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
   f32x2 f = {a, b};
@@ -1494,24 +1498,23 @@ __device__ void plan_units(const PlanArgs& a, uint8_t* lds) {
   int L = (int)max((long long)kSplitMin, (total + share - 1) / share);
   {
     // pieces and longest unit under each candidate length, then the cheapest
-    int n_c[kSplitCands] = {0}, len_c[kSplitCands] = {0};
-    for (int k = k0; k < k1; ++k) {
-      const int c = len_of(row_at(k));
-#pragma unroll
-      for (int i = 0; i < kSplitCands; ++i) {
-        const int Lc = split_cand(L, i), pieces = c > Lc ? (c + Lc - 1) / Lc : 1;
-        n_c[i] += pieces > 1 ? pieces : 0;
-        len_c[i] = max(len_c[i], (c + pieces - 1) / pieces);
-      }
-    }
     const int L0 = L;
     long long best = LLONG_MAX;
-#pragma unroll
+#pragma unroll 1  // (unrolled, its counters push the whole pre-pass past 64 registers)
     for (int i = 0; i < kSplitCands; ++i) {
-      const long long cost = block_sum(n_c[i]) * (4 * kPieceCost) + (long long)a.n_wg * block_max(len_c[i]);
+      const int Lc = split_cand(L0, i);
+      int n = 0, longest = 0;
+#pragma unroll 1
+      for (int k = k0; k < k1; ++k) {
+        const int c = len_of(row_at(k));
+        const int pieces = c > Lc ? (c + Lc - 1) / Lc : 1;
+        n += pieces > 1 ? pieces : 0;
+        longest = max(longest, pieces > 1 ? (c + pieces - 1) / pieces : c);
+      }
+      const long long cost = block_sum(n) * (4 * kPieceCost) + (long long)a.n_wg * block_max(longest);
       if (cost < best) {
         best = cost;
-        L = split_cand(L0, i);
+        L = Lc;
       }
     }
   }
@@ -1690,8 +1693,17 @@ __device__ void plan_units(const PlanArgs& a, uint8_t* lds) {
 template <int D>
 constexpr int kPrepTok = kPrepThreads / (D / 8);
 
-template <int D, bool WITH_V>
-__global__ __launch_bounds__(kPrepThreads) void prep_kernel(const uint4* __restrict__ k, uint4* __restrict__ kt,
+//
+// FRAG (the calls of few rows): the same copies with the 16-byte chunks of every
+// 32-key sub-tile in the order attn_small_kernel's lanes load them, so that each of
+// its loads is 1 KB in one piece (K: [sub-tile][k-step][half][operand row], V^T:
+// [sub-tile][k-step][output tile][half][row]).
+__device__ __forceinline__ int operand_row(int j) {  // of key j of a 32-key sub-tile, and back (see krow)
+  return (j & ~15) | ((j & 15) ^ (((j >> 2) & 3) == 1 || ((j >> 2) & 3) == 2 ? 12 : 0));
+}
+
+template <int D, bool WITH_V, bool FRAG>
+__global__ __launch_bounds__(kPrepThreads, 8) void prep_kernel(const uint4* __restrict__ k, uint4* __restrict__ kt,
                                                             const uint4* __restrict__ v, uint16_t* __restrict__ vt,
                                                             const int32_t* __restrict__ perm, int N, int n_pad,
                                                             int bhs, int pairs_per_wg, PlanArgs pa) {
@@ -1729,7 +1741,12 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const uint4* __restr
       dst[2] = vx.z;
       dst[3] = vx.w;
     }
-    kt[((size_t)bh * n_pad + p0) * CH + t] = kx;
+    int kc = t;  // this chunk's place, from position p0 on
+    if constexpr (FRAG) {
+      const int row = (c & 1) * 32 + operand_row((p0 + j) & 31);
+      kc = ((((p0 + j) & ~31) - p0) * CH) + (c >> 1) * 64 + row;
+    }
+    kt[((size_t)bh * n_pad + p0) * CH + kc] = kx;
     if (bh + 1 < bh1) {
       kx = chunk(k, bh + 1);
       if (WITH_V) vx = chunk(v, bh + 1);
@@ -1742,8 +1759,10 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(const uint4* __restr
       for (int e = 0; e < 4; ++e)
         w[e] = (uint32_t)tile[(tc * 8 + 2 * e) * LS + d] | ((uint32_t)tile[(tc * 8 + 2 * e + 1) * LS + d] << 16);
       const int p = p0 + tc * 8;
-      *(uint4*)(vt + (size_t)bh * n_pad * D + ((size_t)(p / kBK) * D + d) * kBK + p % kBK) =
-          make_uint4(w[0], w[1], w[2], w[3]);
+      size_t at = ((size_t)(p / kBK) * D + d) * kBK + p % kBK;
+      if constexpr (FRAG)
+        at = (size_t)(p / 32) * 32 * D + (((p % 32 / 16) * (D / 32) + d / 32) * 64 + (p % 16 / 8) * 32 + d % 32) * 8;
+      *(uint4*)(vt + (size_t)bh * n_pad * D + at) = make_uint4(w[0], w[1], w[2], w[3]);
     }
   }
 }
@@ -1834,9 +1853,26 @@ int k64_sparse_grid_cap_d(const tra_plan_s& p) {
   return std::max(1, std::max(a, b)) * std::max(p.n_cu, 1);
 }
 
+// Calls that the key-splitting kernel takes (attn_small_kernel): its 4 rows
+// workgroups of 8 waves, one per CU at head_dim 128 (210 registers) and two at 64, fill
+// two rounds of the GPU at most (three at head_dim 64), and one for the fused call,
+// whose own kernel splits the keys in two already.  Measured with every block kept,
+// microseconds of a call without and with it (pre-pass included), 256 CUs:
+//   head_dim 128  8 rows of 8 blocks: dense 31 / 18, fused 27 / 18, entropy 20 / 19;
+//     64 of 16: 52 / 25, 41 / 25, 31 / 17; 128 of 16: 56 / 44, 45 / 46, 34 / 25; 128 of
+//     128: 313 / 198, 204 / 199, 178 / 118; 192 of 16: 63 / 62, 53 / 62; 256 of 16: 64 / 80
+//   head_dim 64  128 rows of 16: 45 / 25, 36 / 26; 192 of 64: 138 / 88, 100 / 95;
+//     256 of 128: 259 / 210, 197 / 220; 512 of 32: 109 / 122
+bool few_rows(const tra_plan_s& p, const AttnArgs& a) {
+  if (a.radius_sq) return false;  // token level: its own kernel
+  const int rounds = a.entropy && a.o ? (p.cfg.head_dim == 64 ? 3 : 1) : p.cfg.head_dim == 64 ? 3 : 2;
+  return (long long)p.rows * (kBQ / kSmallQ) <= (long long)rounds * p.n_cu;
+}
+
 // Rows of at most kSplitMin blocks are never cut: a plan with no more blocks than
-// that needs neither work units nor the merge.
-bool has_units(const tra_plan_s& p, const AttnArgs& a) { return a.sparse && p.NB > kSplitMin; }
+// that needs neither work units nor the merge; nor does one the key-splitting
+// kernel takes.
+bool has_units(const tra_plan_s& p, const AttnArgs& a) { return a.sparse && p.NB > kSplitMin && !few_rows(p, a); }
 
 // At most how many work items a call has: its rows, each cut into the most pieces
 // a list of NB entries can be.  (A grid of as many workgroups as rows would leave
@@ -1857,12 +1893,12 @@ void launch_prep(const tra_plan_s& p, const AttnArgs& a, int grid, hipStream_t s
   const unsigned blocks = (unsigned)per * (unsigned)((bhs + ppw - 1) / ppw) + 1;
   const size_t tile = a.v ? 2 * (size_t)kPrepTok<D> * (D + 2) * sizeof(uint16_t) : 0;
   const size_t lds = std::max(tile, units ? plan_lds_bytes(p.rows) : 0);
-  if (a.v)
-    hipLaunchKernelGGL((prep_kernel<D, true>), dim3(blocks), dim3(kPrepThreads), lds, s, (const uint4*)a.k,
-                       (uint4*)p.d_kt, (const uint4*)a.v, p.d_vt, p.d_perm, p.S, p.n_pad, bhs, ppw, pa);
-  else
-    hipLaunchKernelGGL((prep_kernel<D, false>), dim3(blocks), dim3(kPrepThreads), lds, s, (const uint4*)a.k,
-                       (uint4*)p.d_kt, (const uint4*)a.v, p.d_vt, p.d_perm, p.S, p.n_pad, bhs, ppw, pa);
+  const auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kPrepThreads), lds, s, (const uint4*)a.k, (uint4*)p.d_kt,
+                       (const uint4*)a.v, p.d_vt, p.d_perm, p.S, p.n_pad, bhs, ppw, pa);
+  };
+  if (few_rows(p, a)) a.v ? launch(prep_kernel<D, true, true>) : launch(prep_kernel<D, false, true>);
+  else a.v ? launch(prep_kernel<D, true, false>) : launch(prep_kernel<D, false, false>);
 }
 
 // The unit table of a call, NULL where its rows are its work.
@@ -2148,6 +2184,253 @@ void launch_fused_entropy_output(const tra_plan_s& p, const AttnArgs& a, hipStre
   if (a.ev_stop) (void)hipEventRecord(a.ev_stop, s);
 }
 
+// ------------------------------------------------------------ calls of few rows
+// Calls with too few query-block rows to fill the chip with one workgroup each
+// (see few_rows): every output but the token-level one.  A row's 128 queries are
+// four workgroups of 32, and the 8 waves of a workgroup split its keys: wave w takes
+// sub-tile w % 4 (32 keys) of valid list entries w / 4, w / 4 + 2, ..., with a
+// running state of its own, merged through LDS at the end (as the fp32 kernel
+// does).  Both operands come straight from the tile-major copies into registers,
+// each tile's K and V^T requested one tile ahead, so there is no barrier and no
+// LDS round trip in the loop: in the kernels above a lone workgroup on a CU waits
+// out the latency of every tile copy (about 3,000 cycles a 64-key tile), which is
+// all that their time is at these sizes.  Bound: bytes from the L2 (each 32 queries
+// read all of the row's K and V^T), which is why it stops paying once rows are
+// many (few_rows has the measurements).
+// The split depends on a row's valid entries only, so a list that keeps every block
+// gives the dense call's result bit for bit.
+template <int D, bool SPARSE, bool PV, bool ENT>
+__global__ __launch_bounds__(kSmallThreads, 2) void attn_small_kernel(
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ ktile, const uint16_t* __restrict__ vtile,
+    uint16_t* __restrict__ o, float* __restrict__ lse, float* __restrict__ entropy,
+    const int32_t* __restrict__ perm, const int32_t* __restrict__ cnt, const int32_t* __restrict__ cols,
+    const int32_t* __restrict__ order, const int32_t* __restrict__ bcount, int N, int n_pad, int NB, int rows,
+    float scale_log2) {
+  using G = Geo<D>;
+  constexpr int DT = G::D_TILES, KK = G::QK_STEPS;
+  __shared__ __attribute__((aligned(16))) float sO[PV ? kSmallWaves / 2 : 1][PV ? D * kSmallQ : 4];
+  __shared__ float sStat[kSmallWaves / 2][4][kSmallQ];
+  __shared__ int s_count;
+  extern __shared__ int32_t s_list[];  // the row's valid key blocks
+
+  constexpr int SUBS = kBQ / kSmallQ;
+  int idx = blockIdx.x;
+  if (!(SPARSE && order)) {
+    // workgroup b runs on XCD b mod 8: a contiguous range of query tiles for each
+    const int x = idx & 7, per = rows * SUBS / 8, rem = rows * SUBS % 8;
+    idx = x * per + min(x, rem) + (idx >> 3);
+  }
+  int r = idx / SUBS;
+  const int qsub = idx % SUBS;
+  if (SPARSE && order) {
+    r = order[r];
+    if (r < 0 || r >= rows) return;  // the whole workgroup leaves together
+  }
+  const int bh = r / NB, u = r - bh * NB;
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int col = lane & 31, half = lane >> 5;
+  const int qtok = perm[u * kBQ + qsub * kSmallQ + col];  // -1 at a padding position
+  const bool qvalid = qtok >= 0;
+  if (__ballot(qvalid) == 0) return;  // (every wave holds the same 32 queries)
+  const uint4 zero4 = make_uint4(0, 0, 0, 0);
+  bf16x8 qf[KK];
+  {
+    const uint4* src = (const uint4*)(q + ((size_t)bh * N + max(qtok, 0)) * D);
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) qf[kk] = __builtin_bit_cast(bf16x8, qvalid ? src[2 * kk + half] : zero4);
+  }
+  int count = NB;
+  if constexpr (SPARSE) {
+    if (wave == 0) {
+      const int n = min(max(cnt[r], 0), NB);
+      int kept = 0;
+      for (int i0 = 0; i0 < n; i0 += 64) {
+        const int c = i0 + lane < n ? cols[(size_t)r * NB + i0 + lane] : -1;
+        const bool ok = c >= 0 && c < NB;
+        const uint64_t m = __ballot(ok);
+        if (ok) s_list[kept + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] = c;
+        kept += __popcll(m);
+      }
+      if (lane == 0) s_count = kept;
+    }
+    __syncthreads();
+    count = __builtin_amdgcn_readfirstlane(s_count);
+  }
+
+  const int sub = wave & 3;
+  // sub-tile `sub` of key block 0, in fragment order (see prep_kernel)
+  const uint4* Kb = (const uint4*)(ktile + ((size_t)bh * n_pad + 32 * sub) * D) + lane;
+  const uint4* Vb = (const uint4*)(vtile + ((size_t)bh * n_pad + 32 * sub) * D) + lane;
+  // First entry >= e of this wave's that holds a token in its sub-tile, or count;
+  // *vb its block, *ns its tokens there (they fill the block's first positions).
+  auto next_tile = [&](int e, int* vb, int* ns) -> int {
+    for (; e < count; e += kSmallWaves / 4) {
+      const int c = SPARSE ? __builtin_amdgcn_readfirstlane(s_list[e]) : e;
+      const int n = (bcount ? bcount[c] : min(kBK, N - c * kBK)) - 32 * sub;
+      if (n > 0) {
+        *vb = c;
+        *ns = min(n, 32);
+        return e;
+      }
+    }
+    return count;
+  };
+  uint4 kf[KK], vf[PV ? 2 * DT : 1];
+  auto load_k = [&](int vb) {
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) kf[kk] = Kb[(size_t)vb * (kBK * D / 8) + 64 * kk];
+  };
+  auto load_v = [&](int vb) {
+    if constexpr (PV) {
+#pragma unroll
+      for (int i = 0; i < 2 * DT; ++i)  // k-step i / DT, output tile i % DT
+        vf[i] = Vb[(size_t)vb * (kBK * D / 8) + 64 * i];
+    }
+  };
+
+  f32x16 oacc[PV ? DT : 1];
+#pragma unroll
+  for (int i = 0; i < (PV ? DT : 1); ++i)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) oacc[i][e] = 0.f;
+  RowState st{-INFINITY, 0.f, 0.f, 0.f};
+  int vb = 0, ns = 0, vb_n = 0, ns_n = 0;
+  int e0 = next_tile(wave >> 2, &vb, &ns);
+  if (e0 < count) {
+    load_k(vb);
+    load_v(vb);
+  }
+  while (e0 < count) {
+    const int e1 = next_tile(e0 + kSmallWaves / 4, &vb_n, &ns_n);
+    f32x16 s;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) s[e] = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk)
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kf[kk]), qf[kk], s, 0, 0, 0);
+    if (e1 < count) load_k(vb_n);
+    if (ns < 32) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) s[e] = 16 * (e >> 3) + (e & 7) + 8 * half < ns ? s[e] : -1.0e30f;
+    }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[e]);
+    mx = max_halves(mx);
+    const float m_new = next_reference(st.m, mx * scale_log2);
+    const float sc = __builtin_amdgcn_exp2f(st.m - m_new);
+    if (ENT) st.a = st.l > 0.f ? sc * (st.a + st.l * (st.m - m_new)) : 0.f;
+    st.l *= sc;
+    st.lr *= sc;
+    st.m = m_new;
+    uint32_t pb[8];
+    float lsum = 0.f, asum = 0.f, lr4[4] = {st.lr, 0.f, 0.f, 0.f};
+    tile_exp_acc<PV, ENT>(s, scale_log2, st.m, lsum, asum, lr4, pb);
+    st.l += lsum;
+    if (ENT) st.a += asum;
+    if constexpr (PV) {
+      st.lr = (lr4[0] + lr4[1]) + (lr4[2] + lr4[3]);
+      if (__ballot(sc != 1.0f) != 0) {
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) oacc[dt][e] *= sc;
+      }
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        const bf16x8 p = __builtin_bit_cast(bf16x8, make_uint4(pb[4 * ks], pb[4 * ks + 1], pb[4 * ks + 2], pb[4 * ks + 3]));
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+          oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vf[ks * DT + dt]), p, oacc[dt], 0, 0, 0);
+      }
+      if (e1 < count) load_v(vb_n);
+    }
+    e0 = e1;
+    vb = vb_n;
+    ns = ns_n;
+  }
+
+  // merge the waves' states: waves s..2s-1 into waves 0..s-1, s = 4, 2, 1 (a state
+  // with l = 0 saw no key and contributes nothing)
+  float l = sum_halves(st.l), a = ENT ? sum_halves(st.a) : 0.f, lr = PV ? sum_halves(st.lr) : 0.f, m = st.m;
+#pragma unroll
+  for (int sp = kSmallWaves / 2; sp > 0; sp >>= 1) {
+    if (wave >= sp && wave < 2 * sp) {
+      if constexpr (PV) {
+        float4* dst = (float4*)sO[wave - sp];
+#pragma unroll
+        for (int j = 0; j < 4 * DT; ++j)
+          dst[j * 64 + lane] = make_float4(oacc[j >> 2][4 * (j & 3)], oacc[j >> 2][4 * (j & 3) + 1],
+                                           oacc[j >> 2][4 * (j & 3) + 2], oacc[j >> 2][4 * (j & 3) + 3]);
+      }
+      if (half == 0) {
+        sStat[wave - sp][0][col] = m;
+        sStat[wave - sp][1][col] = l;
+        sStat[wave - sp][2][col] = a;
+        sStat[wave - sp][3][col] = lr;
+      }
+    }
+    __syncthreads();
+    if (wave < sp) {
+      const float m1 = sStat[wave][0][col], l1 = sStat[wave][1][col], a1 = sStat[wave][2][col], lr1 = sStat[wave][3][col];
+      const bool has0 = l != 0.f, has1 = l1 != 0.f;  // (a NaN sum counts as a state)
+      const float mn = has0 ? (has1 ? fmaxf(m, m1) : m) : m1;
+      const float s0 = has0 ? __builtin_amdgcn_exp2f(m - mn) : 0.f, s1 = has1 ? __builtin_amdgcn_exp2f(m1 - mn) : 0.f;
+      if (ENT) a = (has0 ? s0 * (a + l * (m - mn)) : 0.f) + (has1 ? s1 * (a1 + l1 * (m1 - mn)) : 0.f);
+      l = s0 * l + s1 * l1;
+      lr = s0 * lr + s1 * lr1;
+      m = mn;
+      if constexpr (PV) {
+        const float4* src = (const float4*)sO[wave];
+#pragma unroll
+        for (int j = 0; j < 4 * DT; ++j) {
+          const float4 x = src[j * 64 + lane];
+          f32x16& acc = oacc[j >> 2];
+          const int e = 4 * (j & 3);
+          acc[e] = s0 * acc[e] + s1 * x.x;
+          acc[e + 1] = s0 * acc[e + 1] + s1 * x.y;
+          acc[e + 2] = s0 * acc[e + 2] + s1 * x.z;
+          acc[e + 3] = s0 * acc[e + 3] + s1 * x.w;
+        }
+      }
+    }
+    __syncthreads();
+  }
+  if (wave != 0 || !qvalid) return;
+  const size_t tok = (size_t)bh * N + qtok;
+  if constexpr (PV) {
+    const float inv = lr > 0.f ? 1.f / lr : 0.f;
+    uint16_t* dst = o + tok * D;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        uint2 w;
+        w.x = pack_bf16x2(oacc[dt][4 * g] * inv, oacc[dt][4 * g + 1] * inv);
+        w.y = pack_bf16x2(oacc[dt][4 * g + 2] * inv, oacc[dt][4 * g + 3] * inv);
+        *(uint2*)(dst + dt * 32 + 8 * g + 4 * half) = w;
+      }
+  }
+  if (half == 0) {
+    if (ENT) entropy[tok] = 0.69314718055994531f * (__log2f(l) - a / l);
+    if (lse) lse[tok] = l > 0.f ? 0.69314718055994531f * (m + __log2f(l)) : -INFINITY;
+  }
+}
+
+template <int D, bool SPARSE, bool PV, bool ENT>
+void launch_small(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
+  const float scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)D));
+  launch_prep<D>(p, a, 1, s);
+  if (a.ev_start) (void)hipEventRecord(a.ev_start, s);
+  hipLaunchKernelGGL((attn_small_kernel<D, SPARSE, PV, ENT>), dim3(p.rows * (kBQ / kSmallQ)), dim3(kSmallThreads),
+                     SPARSE ? (size_t)p.NB * sizeof(int32_t) : 0, s, (const uint16_t*)a.q, p.d_kt, p.d_vt,
+                     (uint16_t*)a.o, a.lse, a.entropy, p.d_perm, a.cnt, a.cols, a.order,
+                     SPARSE && p.cfg.block_layout == TRA_BLOCKS_TILES ? p.d_bcount : nullptr, p.S, p.n_pad, p.NB,
+                     p.rows, scale_log2);
+  if (a.ev_stop) (void)hipEventRecord(a.ev_stop, s);
+}
+
 template <int D, bool SPARSE, bool PV, bool ENT, int TOK = 0>
 void launch_variant(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
   const float scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)D));
@@ -2175,6 +2458,10 @@ hipError_t launch_bf16_d(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) 
   else if (a.sparse && a.radius_sq && p.cfg.distance == TRA_DIST_1D) launch_variant<D, true, true, false, 2>(p, a, s);
   else if (a.sparse && a.radius_sq && text) launch_variant<D, true, true, false, 5>(p, a, s);
   else if (a.sparse && a.radius_sq) launch_variant<D, true, true, false, 1>(p, a, s);
+  else if (few_rows(p, a) && a.sparse) launch_small<D, true, true, false>(p, a, s);
+  else if (few_rows(p, a) && a.entropy && a.o) launch_small<D, false, true, true>(p, a, s);
+  else if (few_rows(p, a) && a.entropy) launch_small<D, false, false, true>(p, a, s);
+  else if (few_rows(p, a)) launch_small<D, false, true, false>(p, a, s);
   else if (a.sparse) launch_k64<D, true>(p, a, s);
   else if (a.entropy && a.o) launch_fused_entropy_output<D>(p, a, s);
   else if (a.entropy) launch_variant<D, false, false, true>(p, a, s);

@@ -30,9 +30,9 @@ def test_heads_in_turn_equal_one_head(heads, head_dim):
         assert torch.equal(o[:, h:h + 1], o1), h
 
 
-@pytest.mark.parametrize("heads,whole", [(2, False), (8, True)])
+@pytest.mark.parametrize("heads,whole", [(3, False), (8, True)])
 def test_piece_length_follows_the_rows(heads, whole):
-    """Rows of 61 blocks, every block kept: 122 of them are cut in two (the
+    """Rows of 61 blocks, every block kept: 183 of them are cut in two (the
     pieces cost less than the longer tail), 488 are not (cutting them all would
     cost more than it evens out) and equal the dense call bit for bit."""
     import torch
