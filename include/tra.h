@@ -59,8 +59,9 @@
  * words and, for the 2-D distance, the per-key vectors of the token-level key
  * test, and the count lookup table of App. C.1: C(n) for every candidate
  * radius at every position of one octant of the grid, ceil(F/2) ceil(H/2)
- * ceil(W/2) (n_cap + 1) ints -- 331 MB at 21 x 45 x 80 -- or, where that
- * would exceed 1 GiB, C(n_cap) per position); no call writes them, so a plan
+ * ceil(W/2) (n_cap + 1) ints and about 3 % more of padding and search index --
+ * 343 MB at 21 x 45 x 80 -- or, where the counts alone would exceed 1 GiB,
+ * C(n_cap) per position); no call writes them, so a plan
  * is immutable after creation and may be shared by calls on any number of
  * streams at once.
  *

@@ -184,6 +184,7 @@ tra_status tra_plan_destroy(tra_plan p) {
   (void)hipFree(p->d_blocks);
   (void)hipFree(p->d_cap_count);
   (void)hipFree(p->d_ctab);
+  (void)hipFree(p->d_cidx);
   (void)hipFree(p->d_kinfo);
   (void)hipFree(p->d_kfeat);
   if (prev >= 0) (void)hipSetDevice(prev);
@@ -263,9 +264,12 @@ tra_status tra_plan_create(const tra_config* cfg, tra_plan* out) {
       int32_t* disk_tmp = nullptr;
       const size_t disk_bytes = (size_t)((cfg->height + 1) / 2) * ((cfg->width + 1) / 2) * ((size_t)p->n_cap + 1) *
                                 sizeof(int32_t);
-      if ((e = hipMalloc((void**)&p->d_ctab, ctab_bytes)) != hipSuccess ||
+      size_t table_ints, index_ints;
+      tra::count_table_ints(*p, &table_ints, &index_ints);
+      if ((e = hipMalloc((void**)&p->d_ctab, table_ints * sizeof(int32_t))) != hipSuccess ||
+          (e = hipMalloc((void**)&p->d_cidx, index_ints * sizeof(int32_t))) != hipSuccess ||
           (e = hipMalloc((void**)&disk_tmp, disk_bytes)) != hipSuccess ||
-          (e = tra::fill_count_table(*p, p->d_ctab, disk_tmp, nullptr)) != hipSuccess ||
+          (e = tra::fill_count_table(*p, p->d_ctab, p->d_cidx, disk_tmp, nullptr)) != hipSuccess ||
           (e = hipStreamSynchronize(nullptr)) != hipSuccess) {
         (void)hipFree(disk_tmp);
         tra_plan_destroy(p);

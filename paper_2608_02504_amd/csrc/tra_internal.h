@@ -83,6 +83,7 @@ struct tra_plan_s {
   // lookup table), or NULL above kCountTableMaxBytes; then d_cap_count holds
   // C(n_cap) per video position (raster) and the other counts run on the fly
   int32_t* d_ctab = nullptr;
+  int32_t* d_cidx = nullptr;  // the table rows' search index (see radius.hip)
   int32_t* d_cap_count = nullptr;
   // Per-call device memory.  The pointers below marked "call workspace" are
   // NULL in a stored plan, which no call writes; each call works on a copy of
@@ -162,7 +163,9 @@ hipError_t fill_cap_counts(const tra_plan_s& p, int32_t* out, hipStream_t s);
 // fill (disk_tmp: ceil(H/2) ceil(W/2) (n_cap + 1) ints of scratch).
 constexpr size_t kCountTableMaxBytes = (size_t)1 << 30;
 size_t count_table_bytes(const tra_plan_s& p);
-hipError_t fill_count_table(const tra_plan_s& p, int32_t* ctab, int32_t* disk_tmp, hipStream_t s);
+// Ints of the table as stored and of its search index.
+void count_table_ints(const tra_plan_s& p, size_t* table, size_t* index);
+hipError_t fill_count_table(const tra_plan_s& p, int32_t* ctab, int32_t* cidx, int32_t* disk_tmp, hipStream_t s);
 
 hipError_t launch_block_mask(const tra_plan_s& p, const int32_t* radius_sq, uint8_t* mask,
                              int32_t* cnt, int32_t* cols, hipStream_t s);
