@@ -194,6 +194,13 @@ class Plan:
         n, nb, cap = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32()
         _check(lib().tra_plan_dims(h, ctypes.byref(n), ctypes.byref(nb), ctypes.byref(cap)))
         self.n_tokens, self.n_blocks, self.n_cap = n.value, nb.value, cap.value
+        # what every call checks its tensors against, formed once: on small grids
+        # the checks and the marshalling are what a call costs
+        import torch
+        self._qkv_dtype = torch.bfloat16 if cfg.dtype == "bf16" else torch.float32
+        heads = (cfg.batch, cfg.heads)
+        self._tok, self._per = heads + (self.n_tokens, cfg.head_dim), heads + (self.n_tokens,)
+        self._cnt, self._cols = heads + (self.n_blocks,), heads + (self.n_blocks, self.n_blocks)
         self._ws = {}  # stream handle -> workspace tensor of ws_bytes
         self.ws_bytes = max(tra_workspace_size(self, c) for c in _CALLS)
 
@@ -276,97 +283,96 @@ def _ptr(t):
         raise ValueError("tensor must be on the GPU")
     if not t.is_contiguous():
         raise ValueError("tensor must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream(stream):
-    if stream is None:
-        import torch
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
-
-
-def _workspace(plan: Plan, stream, workspace):
-    """(pointer, bytes, tensor) of the workspace for a call on `stream`: the
-    caller's, or the plan's own for that stream (created on first use)."""
+def _current_stream() -> int:
+    """Handle of torch's current stream on the current device (0: the null stream)."""
     import torch
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch._C._cuda_getDevice())  # without the stream object, most of a small call's marshalling
+
+
+def _stream(stream) -> int:
+    if stream is None:
+        return _current_stream()
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+
+
+def _workspace(plan: Plan, handle: int, workspace):
+    """(pointer, bytes) of the workspace for a call on the stream `handle`: the
+    caller's, or the plan's own for that stream (created on first use)."""
     if workspace is not None:
+        import torch
         if workspace.dtype != torch.uint8:
             raise ValueError("workspace must be a uint8 tensor")
-        return _ptr(workspace), workspace.numel(), workspace
+        return _ptr(workspace), workspace.numel()
     if plan.ws_bytes == 0:
-        return None, 0, None
-    handle = _stream(stream).value or 0
+        return None, 0
     ws = plan._ws.get(handle)
     if ws is None:
+        import torch
         ws = torch.empty(plan.ws_bytes, dtype=torch.uint8, device="cuda")
-        if handle != (torch.cuda.current_stream().cuda_stream or 0):
+        if handle != _current_stream():
             # freed only when the plan closes: keep it until that stream's work is done
             ws.record_stream(torch.cuda.ExternalStream(handle))
         plan._ws[handle] = ws
-    return ctypes.c_void_p(ws.data_ptr()), ws.numel(), ws
+    return ws.data_ptr(), plan.ws_bytes
 
 
 def _want(t, shape, dtype, name):
-    if t is None:
-        return
-    if tuple(t.shape) != tuple(shape) or t.dtype != dtype:
+    if t is not None and (t.shape != shape or t.dtype != dtype):
         raise ValueError(f"{name}: expected {tuple(shape)} {dtype}, got {tuple(t.shape)} {t.dtype}")
 
 
-def _qkv_dtype(plan: Plan):
-    import torch
-    return torch.bfloat16 if plan.cfg.dtype == "bf16" else torch.float32
-
-
-def _shapes(plan: Plan):
-    c = plan.cfg
-    return ((c.batch, c.heads, plan.n_tokens, c.head_dim), (c.batch, c.heads, plan.n_tokens),
-            (c.batch, c.heads, plan.n_blocks), (c.batch, c.heads, plan.n_blocks, plan.n_blocks))
+def _want_qkvo(plan: Plan, q, k, v, o):
+    shape, dtype = plan._tok, plan._qkv_dtype
+    _want(q, shape, dtype, "q")
+    _want(k, shape, dtype, "k")
+    _want(v, shape, dtype, "v")
+    _want(o, shape, dtype, "o")
 
 
 def tra_entropy(plan: Plan, q, k, v, o, entropy, stream=None, workspace=None):
     import torch
-    tok, per, _, _ = _shapes(plan)
-    dt = _qkv_dtype(plan)
-    for t, n in ((q, "q"), (k, "k"), (v, "v"), (o, "o")):
-        _want(t, tok, dt, n)
-    _want(entropy, per, torch.float32, "entropy")
-    wp, wn, _ = _workspace(plan, stream, workspace)
+    _want_qkvo(plan, q, k, v, o)
+    _want(entropy, plan._per, torch.float32, "entropy")
+    s = _stream(stream)
+    wp, wn = _workspace(plan, s, workspace)
     _check(lib().tra_entropy(plan.handle, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(entropy),
-                             wp, wn, _stream(stream)))
+                             wp, wn, s))
 
 
 def tra_budget_radius(plan: Plan, entropy, budget, radius_sq, stream=None):
     import torch
-    _, per, _, _ = _shapes(plan)
-    _want(entropy, per, torch.float32, "entropy")
-    _want(budget, per, torch.int32, "budget")
-    _want(radius_sq, per, torch.int32, "radius_sq")
+    _want(entropy, plan._per, torch.float32, "entropy")
+    _want(budget, plan._per, torch.int32, "budget")
+    _want(radius_sq, plan._per, torch.int32, "radius_sq")
     _check(lib().tra_budget_radius(plan.handle, _ptr(entropy), _ptr(budget), _ptr(radius_sq),
                                    _stream(stream)))
 
 
 def tra_build_block_mask(plan: Plan, radius_sq, mask, cnt, cols, order=None, stream=None, workspace=None):
     import torch
-    _, per, rowsh, sq = _shapes(plan)
-    _want(radius_sq, per, torch.int32, "radius_sq")
-    _want(mask, sq, torch.uint8, "mask")
-    _want(cnt, rowsh, torch.int32, "cnt")
-    _want(cols, sq, torch.int32, "cols")
+    _want(radius_sq, plan._per, torch.int32, "radius_sq")
+    _want(mask, plan._cols, torch.uint8, "mask")
+    _want(cnt, plan._cnt, torch.int32, "cnt")
+    _want(cols, plan._cols, torch.int32, "cols")
     _want(order, (plan.rows,), torch.int32, "order")
-    wp, wn, _ = _workspace(plan, stream, workspace) if order is not None else (None, 0, None)
+    s = _stream(stream)
+    wp, wn = _workspace(plan, s, workspace) if order is not None else (None, 0)
     _check(lib().tra_build_block_mask(plan.handle, _ptr(radius_sq), _ptr(mask), _ptr(cnt),
-                                      _ptr(cols), _ptr(order), wp, wn, _stream(stream)))
+                                      _ptr(cols), _ptr(order), wp, wn, s))
 
 
 def tra_build_block_mask_noalloc(plan: Plan, radius_sq, mask, cnt, cols, order=None, stream=None):
     import torch
-    _, per, rowsh, sq = _shapes(plan)
-    _want(radius_sq, per, torch.int32, "radius_sq")
-    _want(mask, sq, torch.uint8, "mask")
-    _want(cnt, rowsh, torch.int32, "cnt")
-    _want(cols, sq, torch.int32, "cols")
+    _want(radius_sq, plan._per, torch.int32, "radius_sq")
+    _want(mask, plan._cols, torch.uint8, "mask")
+    _want(cnt, plan._cnt, torch.int32, "cnt")
+    _want(cols, plan._cols, torch.int32, "cols")
     _want(order, (plan.rows,), torch.int32, "order")
     _check(lib().tra_build_block_mask_noalloc(plan.handle, _ptr(radius_sq), _ptr(mask), _ptr(cnt),
                                               _ptr(cols), _ptr(order), _stream(stream)))
@@ -374,45 +380,39 @@ def tra_build_block_mask_noalloc(plan: Plan, radius_sq, mask, cnt, cols, order=N
 
 def tra_sparse_attention(plan: Plan, q, k, v, cnt, cols, order, o, lse=None, stream=None, workspace=None):
     import torch
-    tok, per, rowsh, sq = _shapes(plan)
-    dt = _qkv_dtype(plan)
-    for t, n in ((q, "q"), (k, "k"), (v, "v"), (o, "o")):
-        _want(t, tok, dt, n)
-    _want(cnt, rowsh, torch.int32, "cnt")
-    _want(cols, sq, torch.int32, "cols")
+    _want_qkvo(plan, q, k, v, o)
+    _want(cnt, plan._cnt, torch.int32, "cnt")
+    _want(cols, plan._cols, torch.int32, "cols")
     _want(order, (plan.rows,), torch.int32, "order")
-    _want(lse, per, torch.float32, "lse")
-    wp, wn, _ = _workspace(plan, stream, workspace)
+    _want(lse, plan._per, torch.float32, "lse")
+    s = _stream(stream)
+    wp, wn = _workspace(plan, s, workspace)
     _check(lib().tra_sparse_attention(plan.handle, _ptr(q), _ptr(k), _ptr(v), _ptr(cnt),
                                       _ptr(cols), _ptr(order), _ptr(o), _ptr(lse), wp, wn,
-                                      _stream(stream)))
+                                      s))
 
 
 def tra_token_attention(plan: Plan, q, k, v, radius_sq, cnt, cols, order, o, lse=None, stream=None,
                         workspace=None):
     import torch
-    tok, per, rowsh, sq = _shapes(plan)
-    dt = _qkv_dtype(plan)
-    for t, n in ((q, "q"), (k, "k"), (v, "v"), (o, "o")):
-        _want(t, tok, dt, n)
-    _want(radius_sq, per, torch.int32, "radius_sq")
-    _want(cnt, rowsh, torch.int32, "cnt")
-    _want(cols, sq, torch.int32, "cols")
+    _want_qkvo(plan, q, k, v, o)
+    _want(radius_sq, plan._per, torch.int32, "radius_sq")
+    _want(cnt, plan._cnt, torch.int32, "cnt")
+    _want(cols, plan._cols, torch.int32, "cols")
     _want(order, (plan.rows,), torch.int32, "order")
-    _want(lse, per, torch.float32, "lse")
-    wp, wn, _ = _workspace(plan, stream, workspace)
+    _want(lse, plan._per, torch.float32, "lse")
+    s = _stream(stream)
+    wp, wn = _workspace(plan, s, workspace)
     _check(lib().tra_token_attention(plan.handle, _ptr(q), _ptr(k), _ptr(v), _ptr(radius_sq),
                                      _ptr(cnt), _ptr(cols), _ptr(order), _ptr(o), _ptr(lse), wp, wn,
-                                     _stream(stream)))
+                                     s))
 
 
 def tra_dense_attention(plan: Plan, q, k, v, o, lse=None, stream=None, workspace=None):
     import torch
-    tok, per, _, _ = _shapes(plan)
-    dt = _qkv_dtype(plan)
-    for t, n in ((q, "q"), (k, "k"), (v, "v"), (o, "o")):
-        _want(t, tok, dt, n)
-    _want(lse, per, torch.float32, "lse")
-    wp, wn, _ = _workspace(plan, stream, workspace)
+    _want_qkvo(plan, q, k, v, o)
+    _want(lse, plan._per, torch.float32, "lse")
+    s = _stream(stream)
+    wp, wn = _workspace(plan, s, workspace)
     _check(lib().tra_dense_attention(plan.handle, _ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse),
-                                     wp, wn, _stream(stream)))
+                                     wp, wn, s))
