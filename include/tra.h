@@ -80,6 +80,8 @@
  *     tables and the split rows' partial results, (head_dim + 3) x 512 bytes for each of up to
  *     32 G + 1 pieces (G the workgroups the GPU holds at once; 1.65 GB at
  *     head_dim 128 on MI355X, less where the plan has fewer blocks);
+ *   tra_dense_attention, in addition, where its last rows are cut: their partial
+ *     results, as above, for at most 16 pieces of each;
  *   tra_build_block_mask with a non-NULL order: the counting-sort histograms
  *     of the row order, 4 x ((NB + 1) x ceil(batch x heads x NB / 256) + 1)
  *     bytes (the only workspace of fp32 plans; with a NULL order the mask call
@@ -353,7 +355,10 @@ tra_status tra_token_attention(tra_plan plan, const void* q, const void* k, cons
                                void* stream);
 
 /* Dense attention o_i = sum_j softmax_j(q_i k_j / sqrt(d)) v_j (Eq. 1), the
- * baseline the sparse call is measured against.  lse as above, or NULL.
+ * baseline the sparse call is measured against.  lse as above, or NULL.  On
+ * plans of more than 48 blocks the rows that would run alone at the end of the
+ * call are computed as up to 16 pieces each and merged, as the sparse call's long
+ * rows are, so they differ from an unsplit computation by rounding only.
  * workspace: TRA_CALL_DENSE. */
 tra_status tra_dense_attention(tra_plan plan, const void* q, const void* k,
                                const void* v, void* o, float* lse, void* workspace,

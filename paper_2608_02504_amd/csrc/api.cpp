@@ -95,6 +95,12 @@ WsLayout ws_layout(const tra_plan_s& p, int call) {
     L.kt = take(kv);
     L.vt = take(kv);
     L.ctr = take(tra::kRowCounters * sizeof(int32_t));
+    if (call == TRA_CALL_DENSE && p.dense_slots > 0) {
+      L.splits = take((size_t)p.dense_splits * 4 * sizeof(int32_t));
+      L.hdr = take(tra::kUnitHdrInts * sizeof(int32_t));
+      L.part = take((size_t)p.dense_slots * 128 * p.cfg.head_dim * sizeof(float));
+      L.pstats = take((size_t)p.dense_slots * 3 * 128 * sizeof(float));
+    }
     if (call == TRA_CALL_SPARSE || call == TRA_CALL_TOKEN) {
       L.units = take((size_t)p.units_cap * 4 * sizeof(int32_t));
       L.splits = take((size_t)p.splits_cap * 4 * sizeof(int32_t));
@@ -130,7 +136,7 @@ tra_status bind_workspace(tra_plan p, int call, bool needed, void* ws, size_t ws
   out->d_kt = (uint16_t*)(b + L.kt);
   out->d_vt = (uint16_t*)(b + L.vt);
   out->d_row_ctr = (int32_t*)(b + L.ctr);
-  if (call == TRA_CALL_SPARSE || call == TRA_CALL_TOKEN) {
+  if (call == TRA_CALL_SPARSE || call == TRA_CALL_TOKEN || (call == TRA_CALL_DENSE && p->dense_slots > 0)) {
     out->d_units = (int32_t*)(b + L.units);
     out->d_splits = (int32_t*)(b + L.splits);
     out->d_unit_hdr = (int32_t*)(b + L.hdr);
@@ -298,6 +304,7 @@ tra_status tra_plan_create(const tra_config* cfg, tra_plan* out) {
       p->split_wg_cap = tra::k64_sparse_grid_cap(*p);
       tra::split_capacities(p->split_wg_cap, p->rows, p->NB, cfg->head_dim, &p->units_cap, &p->splits_cap,
                            &p->slots_cap);
+      tra::dense_capacities(*p, &p->dense_splits, &p->dense_slots);
     }
     // the no-allocation entry point's scratch array on this device: its
     // address is resolved here, once per device, with the device current

@@ -496,6 +496,34 @@ __device__ __forceinline__ int next_row(int32_t* ctr, int rows, int xcd, int& st
   return -1;
 }
 
+// How a dense call's rows are cut: the last `tail` rows of every XCD queue's range
+// into `pieces` pieces of key blocks each (see dense_split).
+struct DenseSplit {
+  int tail, pieces;
+};
+
+// The dense call's queue: as next_row, with the cut rows last, piece-major (piece 0
+// of every cut row, then piece 1, ...).  Returns {row, first key block, end, partial
+// slot or -1}; row -1 once all is drained.
+__device__ __forceinline__ int4 next_dense(int32_t* ctr, int rows, int NB, const DenseSplit& ds, int xcd,
+                                           int& steal) {
+  const int per = rows / 8, rem = rows % 8;
+  while (steal < 8) {
+    const int qd = (xcd + steal) & 7;
+    const int beg = qd * per + min(qd, rem), whole = per + (qd < rem ? 1 : 0) - ds.tail;
+    const int k = atomicAdd(&ctr[qd * 16], 1);
+    if (k < whole) return make_int4(beg + k, 0, NB, -1);
+    const int j = k - whole;
+    if (j < ds.tail * ds.pieces) {
+      const int s = j / ds.tail, i = j - s * ds.tail;
+      return make_int4(beg + whole + i, NB * s / ds.pieces, NB * (s + 1) / ds.pieces,
+                       (qd * ds.tail + i) * ds.pieces + s);
+    }
+    ++steal;
+  }
+  return make_int4(-1, 0, 0, -1);
+}
+
 // Work of a block-sparse or token-level call: the units of the work-unit table
 // (see plan_units), or, on plans whose rows are never cut (units NULL), the rows.
 // (The kernels take the pointers as __restrict__ arguments of their own, which
@@ -1075,8 +1103,8 @@ __device__ __forceinline__ void issue_steps_strided(uint32_t lds_wave, const uin
   }
 }
 
-// One work unit of a row: list positions [beg, end) of row r (the whole row
-// for dense).  slot < 0: the unit is the whole row and writes the normalised
+// One work unit of a row: list positions [beg, end) of row r (key blocks [beg,
+// end) for dense).  slot < 0: the unit is the whole row and writes the normalised
 // output (and lse).  slot >= 0: one piece of a split row; it writes its
 // unnormalised output, running max and sums to partial slot `slot` for the
 // merge kernel.  LSE: also keep the fp32 sum of the weights for the
@@ -1119,7 +1147,7 @@ __device__ __forceinline__ void k64_row(
       qf[kk] = __builtin_bit_cast(bf16x8, x);
     }
   }
-  const int count = SPARSE ? end - beg : NB;
+  const int count = end - beg;
   if constexpr (SPARSE) {
     // a valid entry is staged with its block's token count in the high half
     // (the tokens fill the block's first positions), an invalid one as -1
@@ -1150,7 +1178,7 @@ __device__ __forceinline__ void k64_row(
         c = e & 0xFFFF;
         n = e >> 16;  // -1 for an invalid entry
       } else {
-        c = i >> 1;
+        c = beg + (i >> 1);
         n = min(kBK, N - c * kBK);
       }
       const int nv = n - (i & 1) * kKT;
@@ -1280,7 +1308,7 @@ __device__ __forceinline__ void k64_row(
 
   const float lr_tot = sum_halves(st.lr);
   const float l_tot = LSE ? sum_halves(st.l) : 0.f;
-  if (SPARSE && slot >= 0) {
+  if (slot >= 0) {
     write_partial<D>(oacc, st.m, lr_tot, l_tot, slot, wave * 32 + col, half, part, pstats);
     return;
   }
@@ -1306,13 +1334,15 @@ __device__ __forceinline__ void k64_row(
 // the work-unit table (block-sparse; see plan_units).  Every unit starts
 // with a workgroup barrier (after its block list is staged), which also orders
 // the next s_row write after every wave's read of the current one.
-template <int D, bool SPARSE, bool LSE>
+// CUT (dense only): the call's last rows are cut (dense_split); a variant of its own,
+// so that a call without them keeps its registers.
+template <int D, bool SPARSE, bool LSE, bool CUT = false>
 __global__ __launch_bounds__(kThreads, 3) void attn_k64_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ ktile, const uint16_t* __restrict__ vtile,
     uint16_t* __restrict__ o, float* __restrict__ lse, const int32_t* __restrict__ perm,
     const int32_t* __restrict__ cnt, const int32_t* __restrict__ cols, const int32_t* __restrict__ order,
-    const int32_t* __restrict__ bcount, const int4* __restrict__ units, const int32_t* __restrict__ unit_hdr, int N,
-    int n_pad, int NB, int rows, float scale_log2, int32_t* __restrict__ ctr, float* __restrict__ part,
+    const int32_t* __restrict__ bcount, const int4* __restrict__ units, const int32_t* __restrict__ unit_hdr,
+    DenseSplit ds, int N, int n_pad, int NB, int rows, float scale_log2, int32_t* __restrict__ ctr, float* __restrict__ part,
     float* __restrict__ pstats) {
   const WorkArgs wk{cnt, order, units, unit_hdr, rows, NB};
   constexpr int KT_BYTES = kKT * D * 2;
@@ -1320,28 +1350,36 @@ __global__ __launch_bounds__(kThreads, 3) void attn_k64_kernel(
   __shared__ __attribute__((aligned(1024))) uint8_t smemV[KT_BYTES];
   extern __shared__ int32_t smemCols[];
   __shared__ int s_row, s_steal;  // thread 0's queue state lives in LDS, not in a register
+  __shared__ int4 s_dense;
   if (threadIdx.x == 0) s_steal = 0;
   for (;;) {
     if (threadIdx.x == 0) {
       int steal = s_steal;
-      s_row = SPARSE ? next_work(ctr, wk, blockIdx.x & 7, steal) : next_row(ctr, wk.rows, blockIdx.x & 7, steal);
+      if constexpr (SPARSE) s_row = next_work(ctr, wk, blockIdx.x & 7, steal);
+      else if constexpr (CUT) s_dense = next_dense(ctr, rows, NB, ds, blockIdx.x & 7, steal);
+      else s_row = next_row(ctr, rows, blockIdx.x & 7, steal);
       s_steal = steal;
     }
     __syncthreads();
-    const int w = __builtin_amdgcn_readfirstlane(s_row);
-    if (w < 0) break;
+    int4 un;
     if constexpr (SPARSE) {
-      const int4 un = work_at(wk, w);
+      const int w = __builtin_amdgcn_readfirstlane(s_row);
+      if (w < 0) break;
+      un = work_at(wk, w);
       if (un.x < 0) {
         __syncthreads();
         continue;
       }
-      k64_row<D, true, LSE>(un.x, un.y, un.z, un.w, smemK, smemV, smemCols, q, ktile, vtile, o, lse, perm, cols,
-                            bcount, N, n_pad, NB, scale_log2, part, pstats);
+    } else if constexpr (CUT) {
+      un = make_int4(__builtin_amdgcn_readfirstlane(s_dense.x), __builtin_amdgcn_readfirstlane(s_dense.y),
+                     __builtin_amdgcn_readfirstlane(s_dense.z), __builtin_amdgcn_readfirstlane(s_dense.w));
+      if (un.x < 0) break;
     } else {
-      k64_row<D, false, LSE>(w, 0, NB, -1, smemK, smemV, smemCols, q, ktile, vtile, o, lse, perm, cols, bcount,
-                             N, n_pad, NB, scale_log2, part, pstats);
+      un = make_int4(__builtin_amdgcn_readfirstlane(s_row), 0, NB, -1);
+      if (un.x < 0) break;
     }
+    k64_row<D, SPARSE, LSE>(un.x, un.y, un.z, un.w, smemK, smemV, smemCols, q, ktile, vtile, o, lse, perm, cols,
+                            bcount, N, n_pad, NB, scale_log2, part, pstats);
   }
 }
 
@@ -1413,6 +1451,7 @@ struct PlanArgs {
   int4* splits;
   int32_t* hdr;
   int32_t* ctr;
+  DenseSplit dense;  // a dense call's cut rows (tail 0: none)
 };
 
 constexpr int kPrepThreads = 1024;
@@ -1711,7 +1750,17 @@ __global__ __launch_bounds__(kPrepThreads, 8) void prep_kernel(const uint4* __re
   const int t = threadIdx.x;
   if (blockIdx.x == 0) {
     if (t < kRowCounters) pa.ctr[t] = 0;
-    if (pa.cnt) plan_units(pa, lds);
+    if (pa.cnt) {
+      plan_units(pa, lds);
+    } else if (pa.dense.tail > 0) {  // the cut rows, for the merge
+      const int per = pa.rows / 8, rem = pa.rows % 8, n = 8 * pa.dense.tail;
+      for (int e = t; e < n; e += kPrepThreads) {
+        const int qd = e / pa.dense.tail, i = e - qd * pa.dense.tail;
+        const int end = (qd + 1) * per + min(qd + 1, rem);
+        pa.splits[e] = make_int4(end - pa.dense.tail + i, e * pa.dense.pieces, pa.dense.pieces, 0);
+      }
+      if (t == 0) pa.hdr[1] = n;
+    }
     return;
   }
   constexpr int TOK = kPrepTok<D>, CH = D / 8, LS = D + 2;
@@ -1883,10 +1932,10 @@ long long most_work(const tra_plan_s& p, const AttnArgs& a) {
 
 // The pre-pass of a call whose work is cut for `grid` workgroups.
 template <int D>
-void launch_prep(const tra_plan_s& p, const AttnArgs& a, int grid, hipStream_t s) {
+void launch_prep(const tra_plan_s& p, const AttnArgs& a, int grid, hipStream_t s, DenseSplit ds = {0, 1}) {
   const bool units = has_units(p, a);
   const PlanArgs pa{units ? a.cnt : nullptr, a.order, p.rows, p.NB, grid, p.units_cap, p.splits_cap, p.slots_cap,
-                    (int4*)p.d_units, (int4*)p.d_splits, p.d_unit_hdr, p.d_row_ctr};
+                    (int4*)p.d_units, (int4*)p.d_splits, p.d_unit_hdr, p.d_row_ctr, ds};
   // up to eight pairs a workgroup, as long as 16 workgroups a CU are left
   const int bhs = p.cfg.batch * p.cfg.heads, per = p.n_pad / kPrepTok<D>;
   const int ppw = (int)std::min<long long>(8, std::max<long long>(1, (long long)per * bhs / (16 * std::max(p.n_cu, 1))));
@@ -1906,9 +1955,36 @@ const int4* unit_table(const tra_plan_s& p, const AttnArgs& a) {
   return has_units(p, a) ? (const int4*)p.d_units : nullptr;
 }
 
+// The cut of a dense call for `cap` resident workgroups.  Its rows are equal, so a
+// queue of n rows for its g = cap / 8 workgroups takes ceil(n / g) rounds, the last
+// one with n mod g rows: those rows (or, with fewer than g, all) are cut into the
+// number of pieces, up to 16 of at least kSplitMin key blocks, that leaves the
+// fewest rounds, each piece counted at kPieceCost blocks more.  Only where the
+// last round has at least one row per CU (three workgroups each), or is the only one
+// and leaves room for three pieces: fewer rows finish at a higher clock than the
+// full GPU's, which runs at its power limit, and cutting them gains nothing.  Rows of
+// at most kSplitMin blocks stay whole, as in the block-sparse call.  Measured,
+// microseconds uncut and cut, head_dim 128, 768 workgroups: 256 rows of 256 blocks
+// 653 / 537, 1,113 of 159 1,401 / 1,287, 1,182 of 591 5,304 / 4,920, 2,787 of 929 18,889 /
+// 18,118; not cut: 1,773 of 591 (29 rows a queue left) 7,556 / 7,953, 196 of 98 267 / 279.
+DenseSplit dense_split(int rows, int NB, int cap) {
+  const int n = rows / 8, g = std::max(1, cap / 8), tail = n % g;
+  DenseSplit best{0, 1};
+  if (n < g ? NB < 3 * kSplitMin : 3 * tail < g) return best;
+  double least = 1.0;  // rounds of the last rows, uncut
+  for (int p = 2; p <= 16 && NB / p >= kSplitMin; ++p) {
+    const double rounds = (double)((tail * p + g - 1) / g) / p + (double)kPieceCost * tail * p / ((double)g * NB);
+    if (rounds < least) {
+      least = rounds;
+      best = DenseSplit{tail, p};
+    }
+  }
+  return best;
+}
+
 template <int D>
-void launch_merge(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
-  const dim3 grid(std::max(1, (int)std::min<long long>((long long)p.splits_cap * (kBQ / kMergeQueries<D>), 16LL * p.n_cu)));
+void launch_merge(const tra_plan_s& p, const AttnArgs& a, long long splits, hipStream_t s) {
+  const dim3 grid(std::max(1, (int)std::min<long long>(splits * (kBQ / kMergeQueries<D>), 16LL * p.n_cu)));
   if (a.lse)
     hipLaunchKernelGGL((merge_split_rows_kernel<D, true>), grid, dim3(256), 0, s, (const int4*)p.d_splits,
                        p.d_unit_hdr, p.d_part, p.d_pstats, (uint16_t*)a.o, a.lse, p.d_perm, p.S, p.NB);
@@ -1917,21 +1993,36 @@ void launch_merge(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
                        p.d_unit_hdr, p.d_part, p.d_pstats, (uint16_t*)a.o, a.lse, p.d_perm, p.S, p.NB);
 }
 
-template <int D, bool SPARSE, bool LSE>
-void launch_k64_lse(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
+template <int D, bool SPARSE, bool LSE, bool CUT>
+void launch_k64_kernel(const tra_plan_s& p, const AttnArgs& a, int cap, DenseSplit ds, hipStream_t s) {
   const float scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)D));
   const size_t lds_bytes = SPARSE ? (size_t)p.NB * sizeof(int32_t) : 0;
-  const int cap = std::min(resident_grid(attn_k64_kernel<D, SPARSE, LSE>, lds_bytes, p, INT_MAX),
-                           SPARSE ? p.split_wg_cap : INT_MAX);
-  const int grid = (int)std::min<long long>(cap, most_work(p, a));
-  launch_prep<D>(p, a, cap, s);
+  const int grid = (int)std::min<long long>(cap, most_work(p, a) + 8LL * ds.tail * (ds.pieces - 1));
+  launch_prep<D>(p, a, cap, s, ds);
   if (a.ev_start) (void)hipEventRecord(a.ev_start, s);
-  hipLaunchKernelGGL((attn_k64_kernel<D, SPARSE, LSE>), dim3(grid), dim3(kThreads), lds_bytes, s,
+  hipLaunchKernelGGL((attn_k64_kernel<D, SPARSE, LSE, CUT>), dim3(grid), dim3(kThreads), lds_bytes, s,
                      (const uint16_t*)a.q, p.d_kt, p.d_vt, (uint16_t*)a.o, a.lse, p.d_perm, a.cnt, a.cols, a.order,
-                     p.cfg.block_layout == TRA_BLOCKS_TILES ? p.d_bcount : nullptr, unit_table(p, a), p.d_unit_hdr,
+                     p.cfg.block_layout == TRA_BLOCKS_TILES ? p.d_bcount : nullptr, unit_table(p, a), p.d_unit_hdr, ds,
                      p.S, p.n_pad, p.NB, p.rows, scale_log2, p.d_row_ctr, p.d_part, p.d_pstats);
   if (a.ev_stop) (void)hipEventRecord(a.ev_stop, s);
-  if (has_units(p, a)) launch_merge<D>(p, a, s);
+}
+
+template <int D, bool SPARSE, bool LSE>
+void launch_k64_lse(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
+  const size_t lds_bytes = SPARSE ? (size_t)p.NB * sizeof(int32_t) : 0;
+  if constexpr (!SPARSE) {
+    const int cap = resident_grid(attn_k64_kernel<D, false, LSE, true>, 0, p, INT_MAX);
+    const DenseSplit ds = dense_split(p.rows, p.NB, cap);
+    if (ds.tail > 0 && 8 * ds.tail * ds.pieces <= p.dense_slots) {  // (always within the plan's bound)
+      launch_k64_kernel<D, false, LSE, true>(p, a, cap, ds, s);
+      launch_merge<D>(p, a, 8LL * ds.tail, s);
+      return;
+    }
+  }
+  const int cap = std::min(resident_grid(attn_k64_kernel<D, SPARSE, LSE>, lds_bytes, p, INT_MAX),
+                           SPARSE ? p.split_wg_cap : INT_MAX);
+  launch_k64_kernel<D, SPARSE, LSE, false>(p, a, cap, DenseSplit{0, 1}, s);
+  if (has_units(p, a)) launch_merge<D>(p, a, p.splits_cap, s);
 }
 
 template <int D, bool SPARSE>
@@ -2448,7 +2539,7 @@ void launch_variant(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
                      a.cols, a.order, unit_table(p, a), p.d_unit_hdr, p.S, p.n_pad, p.NB, p.rows, scale_log2, tk,
                      p.d_row_ctr, p.d_part, p.d_pstats);
   if (a.ev_stop) (void)hipEventRecord(a.ev_stop, s);
-  if (has_units(p, a)) launch_merge<D>(p, a, s);
+  if (has_units(p, a)) launch_merge<D>(p, a, p.splits_cap, s);
 }
 
 template <int D>
@@ -2470,6 +2561,22 @@ hipError_t launch_bf16_d(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) 
 }
 
 }  // namespace
+
+void dense_capacities(const tra_plan_s& p, int* splits, int* slots) {
+  *splits = *slots = 0;
+  const auto take = [&](auto kernel) {
+    const DenseSplit ds = dense_split(p.rowsa, p.NBa, resident_grid(kernel, 0, p, INT_MAX));
+    *splits = std::max(*splits, 8 * ds.tail);
+    *slots = std::max(*slots, 8 * ds.tail * ds.pieces);
+  };
+  if (p.cfg.head_dim == 64) {
+    take(attn_k64_kernel<64, false, false, true>);
+    take(attn_k64_kernel<64, false, true, true>);
+  } else {
+    take(attn_k64_kernel<128, false, false, true>);
+    take(attn_k64_kernel<128, false, true, true>);
+  }
+}
 
 int k64_sparse_grid_cap(const tra_plan_s& p) {
   return p.cfg.head_dim == 64 ? k64_sparse_grid_cap_d<64>(p) : k64_sparse_grid_cap_d<128>(p);

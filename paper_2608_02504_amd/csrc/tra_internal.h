@@ -118,6 +118,7 @@ struct tra_plan_s {
   // (running max, rounded and fp32 sums), for at most split_wg_cap workgroups;
   // the capacities are the plan's, fixed at creation.
   int32_t split_wg_cap = 0, units_cap = 0, splits_cap = 0, slots_cap = 0;
+  int32_t dense_splits = 0, dense_slots = 0;  // the dense call's cut rows and pieces
   int32_t* d_units = nullptr;
   int32_t* d_splits = nullptr;
   int32_t* d_unit_hdr = nullptr;
@@ -152,6 +153,8 @@ hipError_t launch_attention_bf16(const tra_plan_s& p, const AttnArgs& a, hipStre
 int k64_sparse_grid_cap(const tra_plan_s& p);
 void split_capacities(int grid_cap, int rows, int NB, int head_dim, int* units_cap, int* splits_cap,
                       int* slots_cap);
+// The most cut rows and pieces a dense call of this plan has.
+void dense_capacities(const tra_plan_s& p, int* splits, int* slots);
 constexpr int kUnitHdrInts = 16;  // header of the work-unit tables
 hipError_t launch_attention_f32(const tra_plan_s& p, const AttnArgs& a, hipStream_t s);
 

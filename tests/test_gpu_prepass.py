@@ -51,3 +51,36 @@ def test_piece_length_follows_the_rows(heads, whole):
     # bf16 outputs of the same sums: an ulp or two of values below 1
     assert (o.float() - d.float()).abs().max() <= 2 ** -7
     assert (lse - lse_d).abs().max() <= 1e-5 * lse_d.abs().max()
+
+
+@pytest.mark.parametrize("head_dim,frames", [(128, 13), (64, 13), (128, 21)])
+def test_dense_cut_rows(head_dim, frames):
+    """A dense call whose last rows are cut into pieces (159 blocks x 2 heads: every
+    row; 256 x 5 heads: the rows past the GPU's last full round) against the
+    oracle on blocks at both ends of the queues' ranges, and against one-head
+    plans, which the key-splitting kernel takes or cut elsewhere."""
+    import numpy as np
+    import torch
+    import paper_2608_02504_amd as tra
+    import synth
+    from _pipeline import TOL_O_BF16, OracleTables, dense_reference, torch_inputs
+    import oracle as O
+    heads = 2 if frames == 13 else 5
+    w = synth.Workload("dense_cut", 1, heads, head_dim, "bf16", frames, 30, 52, 128, 0.25, 4.0, 0.6, seed=41,
+                       tile_h=8, tile_w=16)
+    inputs = synth.generate(w)
+    q, k, v = torch_inputs(w, *inputs)
+    plan, one = (tra.Plan(tra.Config.from_workload(w.replace(heads=n))) for n in (heads, 1))
+    o, lse = torch.empty_like(q), torch.empty(1, heads, w.n_tokens, device="cuda")
+    tra.tra_dense_attention(plan, q, k, v, o, lse)
+    o1, lse1 = torch.empty_like(q[:, :1]), torch.empty(1, 1, w.n_tokens, device="cuda")
+    perm, NB = OracleTables(w).perm, plan.n_blocks
+    for h in range(heads):
+        tra.tra_dense_attention(one, *(t[:, h:h + 1].contiguous() for t in (q, k, v)), o1, lse1)
+        assert (o[:, h:h + 1].float() - o1.float()).abs().max() <= TOL_O_BF16
+        assert (lse[:, h:h + 1] - lse1).abs().max() <= 1e-4 + 1e-5 * lse1.abs().max()
+        if h in (0, heads - 1):
+            rows = np.concatenate([O.block_tokens(perm, 128, u) for u in (0, NB // 2, NB - 1)])
+            _, want, want_lse = dense_reference(*(synth.to_f64(a[0, h], "bf16") for a in inputs), rows)
+            assert np.abs(o[0, h].float().cpu().numpy()[rows] - want).max() <= TOL_O_BF16
+            assert np.abs(lse[0, h].cpu().numpy()[rows] - want_lse).max() <= 1e-4 + 1e-5 * np.abs(want_lse).max()
