@@ -190,7 +190,6 @@ tra_status tra_plan_destroy(tra_plan p) {
   (void)hipFree(p->d_blocks);
   (void)hipFree(p->d_cap_count);
   (void)hipFree(p->d_ctab);
-  (void)hipFree(p->d_cidx);
   (void)hipFree(p->d_kinfo);
   (void)hipFree(p->d_kfeat);
   if (prev >= 0) (void)hipSetDevice(prev);
@@ -272,16 +271,16 @@ tra_status tra_plan_create(const tra_config* cfg, tra_plan* out) {
                                 sizeof(int32_t);
       size_t table_ints, index_ints;
       tra::count_table_ints(*p, &table_ints, &index_ints);
-      if ((e = hipMalloc((void**)&p->d_ctab, table_ints * sizeof(int32_t))) != hipSuccess ||
-          (e = hipMalloc((void**)&p->d_cidx, index_ints * sizeof(int32_t))) != hipSuccess ||
+      if ((e = hipMalloc((void**)&p->d_ctab, (table_ints + index_ints) * sizeof(int32_t))) != hipSuccess ||
           (e = hipMalloc((void**)&disk_tmp, disk_bytes)) != hipSuccess ||
-          (e = tra::fill_count_table(*p, p->d_ctab, p->d_cidx, disk_tmp, nullptr)) != hipSuccess ||
+          (e = tra::fill_count_table(*p, p->d_ctab, p->d_ctab + table_ints, disk_tmp, nullptr)) != hipSuccess ||
           (e = hipStreamSynchronize(nullptr)) != hipSuccess) {
         (void)hipFree(disk_tmp);
         tra_plan_destroy(p);
         return fail(TRA_ERR_ALLOC, std::string("plan count table: ") + hipGetErrorString(e));
       }
       (void)hipFree(disk_tmp);
+      p->d_cidx = p->d_ctab + table_ints;
     } else if ((e = hipMalloc((void**)&p->d_cap_count, (size_t)std::max(p->N, 1) * sizeof(int32_t))) != hipSuccess ||
                (e = tra::fill_cap_counts(*p, p->d_cap_count, nullptr)) != hipSuccess ||
                (e = hipStreamSynchronize(nullptr)) != hipSuccess) {

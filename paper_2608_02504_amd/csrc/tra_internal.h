@@ -83,7 +83,7 @@ struct tra_plan_s {
   // lookup table), or NULL above kCountTableMaxBytes; then d_cap_count holds
   // C(n_cap) per video position (raster) and the other counts run on the fly
   int32_t* d_ctab = nullptr;
-  int32_t* d_cidx = nullptr;  // the table rows' search index (see radius.hip)
+  int32_t* d_cidx = nullptr;  // the table rows' search index (see radius.hip), in the same allocation
   int32_t* d_cap_count = nullptr;
   // Per-call device memory.  The pointers below marked "call workspace" are
   // NULL in a stored plan, which no call writes; each call works on a copy of
