@@ -84,3 +84,31 @@ def test_dense_cut_rows(head_dim, frames):
             _, want, want_lse = dense_reference(*(synth.to_f64(a[0, h], "bf16") for a in inputs), rows)
             assert np.abs(o[0, h].float().cpu().numpy()[rows] - want).max() <= TOL_O_BF16
             assert np.abs(lse[0, h].cpu().numpy()[rows] - want_lse).max() <= 1e-4 + 1e-5 * np.abs(want_lse).max()
+
+
+@pytest.mark.parametrize("heads", [620, 700])
+def test_plan_of_many_rows(heads):
+    """31,000 rows, whose lengths the plan of the work units keeps in LDS (62 KB
+    of them), and 35,000, which it reads from memory: short rows and, every 97th,
+    one of all 50 blocks, which is cut.  First, middle and last head against a
+    one-head plan."""
+    import torch
+    import paper_2608_02504_amd as tra
+    cfg = dict(frames=5, height=32, width=40, head_dim=64)
+    plan, one = tra.Plan(tra.Config(1, heads, **cfg)), tra.Plan(tra.Config(1, 1, **cfg))
+    S, NB = plan.n_tokens, plan.n_blocks
+    assert NB == 50 and plan.rows == 50 * heads
+    g = torch.Generator(device="cuda").manual_seed(9)
+    q, k, v = (torch.randn(1, heads, S, 64, generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    long = (torch.arange(heads * NB, device="cuda") % 97 == 0).view(1, heads, NB)
+    cnt = torch.where(long, NB, 2).int()
+    u = torch.arange(NB, device="cuda")
+    cols = u.expand(1, heads, NB, NB).clone().int()
+    cols[..., :2] = torch.where(long[..., None], cols[..., :2], torch.stack([u.clamp(max=NB - 2), u.clamp(max=NB - 2) + 1], 1).int())
+    o, o1 = torch.empty_like(q), torch.empty_like(q[:, :1])
+    tra.tra_sparse_attention(plan, q, k, v, cnt, cols, None, o)
+    for h in (0, heads // 2, heads - 1):
+        tra.tra_sparse_attention(one, *(t[:, h:h + 1].contiguous() for t in (q, k, v, cnt, cols)), None, o1)
+        # bf16 outputs of the same sums in another order (|v| up to 5): two ulps
+        assert (o[:, h:h + 1].float() - o1.float()).abs().max() <= 2 ** -4, h
+        assert (o[:, h:h + 1].float() - o1.float()).norm() <= 1e-2 * o1.float().norm()
