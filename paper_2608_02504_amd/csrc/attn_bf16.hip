@@ -1361,25 +1361,28 @@ __global__ __launch_bounds__(kThreads, 3) void attn_k64_kernel(
       s_steal = steal;
     }
     __syncthreads();
-    int4 un;
-    if constexpr (SPARSE) {
-      const int w = __builtin_amdgcn_readfirstlane(s_row);
-      if (w < 0) break;
-      un = work_at(wk, w);
-      if (un.x < 0) {
-        __syncthreads();
-        continue;
-      }
-    } else if constexpr (CUT) {
-      un = make_int4(__builtin_amdgcn_readfirstlane(s_dense.x), __builtin_amdgcn_readfirstlane(s_dense.y),
-                     __builtin_amdgcn_readfirstlane(s_dense.z), __builtin_amdgcn_readfirstlane(s_dense.w));
-      if (un.x < 0) break;
+    if constexpr (CUT) {
+      const int r = __builtin_amdgcn_readfirstlane(s_dense.x);
+      if (r < 0) break;
+      k64_row<D, false, LSE>(r, __builtin_amdgcn_readfirstlane(s_dense.y), __builtin_amdgcn_readfirstlane(s_dense.z),
+                             __builtin_amdgcn_readfirstlane(s_dense.w), smemK, smemV, smemCols, q, ktile, vtile, o,
+                             lse, perm, cols, bcount, N, n_pad, NB, scale_log2, part, pstats);
     } else {
-      un = make_int4(__builtin_amdgcn_readfirstlane(s_row), 0, NB, -1);
-      if (un.x < 0) break;
+      const int w = s_row;
+      if (w < 0) break;
+      if constexpr (SPARSE) {
+        const int4 un = work_at(wk, __builtin_amdgcn_readfirstlane(w));
+        if (un.x < 0) {
+          __syncthreads();
+          continue;
+        }
+        k64_row<D, true, LSE>(un.x, un.y, un.z, un.w, smemK, smemV, smemCols, q, ktile, vtile, o, lse, perm, cols,
+                              bcount, N, n_pad, NB, scale_log2, part, pstats);
+      } else {
+        k64_row<D, false, LSE>(w, 0, NB, -1, smemK, smemV, smemCols, q, ktile, vtile, o, lse, perm, cols, bcount, N,
+                               n_pad, NB, scale_log2, part, pstats);
+      }
     }
-    k64_row<D, SPARSE, LSE>(un.x, un.y, un.z, un.w, smemK, smemV, smemCols, q, ktile, vtile, o, lse, perm, cols,
-                            bcount, N, n_pad, NB, scale_log2, part, pstats);
   }
 }
 
