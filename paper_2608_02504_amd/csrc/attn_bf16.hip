@@ -1819,10 +1819,11 @@ __global__ __launch_bounds__(kPrepThreads, 8) void prep_kernel(const uint4* __re
   }
 }
 
-// Merges the pieces of the split rows: m = max over pieces of m_p (pieces
-// with no weight skipped), w_p = 2^(m_p - m), o = sum_p w_p O_p / sum_p w_p lr_p
-// (the rounded sums the pieces' bf16 weights add up to), lse = ln 2 (m +
-// log2 sum_p w_p l_p).  A thread takes four components of one query, a workgroup
+// Merges the pieces of the split rows: m = max over pieces of m_p, w_p = 2^(m_p -
+// m), o = sum_p w_p O_p / sum_p w_p lr_p (the rounded sums the pieces' bf16 weights
+// add up to), lse = ln 2 (m + log2 sum_p w_p l_p).  A piece that saw no key has m_p =
+// -inf and is skipped; every other one counts, a sum of 0 or NaN included, so that a
+// row holds what it would uncut.  A thread takes four components of one query, a workgroup
 // 1024 / D queries of a split row, one after another over the pieces with eight
 // pieces' loads in flight: what bounds it is the chain of those loads where few rows
 // are split and the bytes (68 KB a piece) where many are.  One workgroup per whole
@@ -1854,7 +1855,7 @@ __global__ __launch_bounds__(256) void merge_split_rows_kernel(const int4* __res
 #pragma unroll 8
     for (int p = 0; p < pieces; ++p) {
       const float* ps = ps0 + (size_t)p * 3 * kBQ;
-      m = ps[kBQ] > 0.f ? fmaxf(m, ps[0]) : m;
+      m = fmaxf(m, ps[0]);
     }
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     float lr = 0.f, lf = 0.f;
@@ -1862,10 +1863,9 @@ __global__ __launch_bounds__(256) void merge_split_rows_kernel(const int4* __res
     for (int p = 0; p < pieces; ++p) {
       const float* ps = ps0 + (size_t)p * 3 * kBQ;
       const float4 x = *(const float4*)(po0 + (size_t)p * kBQ * D);
-      const float lrp = ps[kBQ];
-      const bool used = lrp > 0.f;  // (a piece with no weight adds nothing, whatever its sums hold)
+      const bool used = ps[0] > -INFINITY;
       const float w = used ? __builtin_amdgcn_exp2f(ps[0] - m) : 0.f;
-      lr += used ? w * lrp : 0.f;
+      lr += used ? w * ps[kBQ] : 0.f;
       if (LSE) lf += used ? w * ps[2 * kBQ] : 0.f;
       acc.x += used ? w * x.x : 0.f;
       acc.y += used ? w * x.y : 0.f;
