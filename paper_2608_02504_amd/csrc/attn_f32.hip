@@ -283,6 +283,12 @@ __global__ __launch_bounds__(kF32Threads, 2) void attn_f32_kernel(F32Params P) {
     if (ENT) a += as;
     m = mn;
     if constexpr (PV) {
+      if (ns < kTile) {  // rows past the last token: 0 times the repeated one would be NaN where it is infinite
+        const int left = opaque(ns - 4 * half);
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          if (key_of(e) >= left) buf[e] = vecv(0.f);
+      }
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
 #pragma unroll

@@ -75,3 +75,36 @@ def test_cut_rows_keep_nan_and_infinity(workload, call):
     inf[3, touched, 5] = True
     assert torch.equal(o[0] == float("inf"), inf)
     assert (o[0] != -float("inf")).all() and lse[0, [0, 3, 4, 5, 6]].isfinite().all()
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_fp32_infinite_last_value(head_dim):
+    """An infinite value in the last token of a partial 32-key tile (45 and 77
+    tokens: 13 in the last) makes its component infinite, not NaN."""
+    import torch
+    import paper_2608_02504_amd as tra
+    for h in (5, 7):
+        plan = tra.Plan(tra.Config(1, 1, 1, h, 9 if h == 5 else 11, head_dim, block=64, tile_h=8, tile_w=8, dtype="fp32"))
+        S, NB = plan.n_tokens, plan.n_blocks
+        assert S % 32 == 13
+        g = torch.Generator(device="cuda").manual_seed(1)
+        q, k, v = (torch.randn(1, 1, S, head_dim, generator=g, device="cuda") for _ in range(3))
+        last = int(O.tile_major_order(1, h, 9 if h == 5 else 11, 8, 8)[-1])
+        v[0, 0, last, 3] = float("inf")
+        want = torch.zeros(S, head_dim, dtype=torch.bool, device="cuda")
+        want[:, 3] = True
+        cnt = torch.full((1, 1, NB), NB, dtype=torch.int32, device="cuda")
+        cols = torch.arange(NB, dtype=torch.int32, device="cuda").expand(1, 1, NB, NB).contiguous()
+        full = torch.full((1, 1, S), tra.TRA_RADIUS_FULL, dtype=torch.int32, device="cuda")
+        for call in ("dense", "entropy", "sparse", "token"):
+            o = torch.empty_like(q)
+            if call == "dense":
+                tra.tra_dense_attention(plan, q, k, v, o)
+            elif call == "entropy":
+                tra.tra_entropy(plan, q, k, v, o, torch.empty(1, 1, S, device="cuda"))
+            elif call == "sparse":
+                tra.tra_sparse_attention(plan, q, k, v, cnt, cols, None, o)
+            else:
+                tra.tra_token_attention(plan, q, k, v, full, cnt, cols, None, o)
+            assert not o.isnan().any(), (call, h)
+            assert torch.equal(o[0, 0] == float("inf"), want), (call, h)
