@@ -185,11 +185,18 @@ __global__ __launch_bounds__(kF32Threads, 2) void attn_f32_kernel(F32Params P) {
   auto key_token = [&](int pos, int ns) { return P.perm[pos + min(col, ns - 1)]; };
 
   f32x16 oacc[PV ? DT : 1];
+  float m, l, a;
+  // (TOK) A query takes nothing from a tile of which it covers no key, but 0 times an
+  // infinite or NaN value is NaN: a wave whose output is not finite goes over its
+  // tiles once more, carefully, putting such queries' sums back after each.
+  [[maybe_unused]] bool careful = false;
+again:
 #pragma unroll
   for (int i = 0; i < (PV ? DT : 1); ++i)
 #pragma unroll
     for (int e = 0; e < 16; ++e) oacc[i][e] = 0.f;
-  float m = -INFINITY, l = 0.f, a = 0.f;
+  m = -INFINITY;
+  l = a = 0.f;
 
   // buf: the current tile's K (16 / KC entries per chunk); as a chunk of it is
   // consumed by QK^T, rows of the tile's V take its place, and as those are
@@ -244,6 +251,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void attn_f32_kernel(F32Params P) {
     }
 
     float mc = -INFINITY;
+    [[maybe_unused]] bool some = false;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       bool keep = half16 + 4 * key_of(e) < 4 * ns;
@@ -252,8 +260,15 @@ __global__ __launch_bounds__(kF32Threads, 2) void attn_f32_kernel(F32Params P) {
         const int32_t cw_j = from_lane(cw, half16 + 4 * key_of(e));
         if (keep && !all_keys && tok_j < P.Nv) keep = covers<TOK>(P, cw_i, qtok, n_i, cw_j, tok_j);
       }
+      if (TOK != 0) some = some || keep;
       s[e] = keep ? s[e] * P.alpha : -INFINITY;
       mc = fmaxf(mc, s[e]);
+    }
+    // (TOK) the queries that cover a key of the tile
+    [[maybe_unused]] uint64_t takes = ~0ull;
+    if constexpr (TOK != 0) {
+      takes = __ballot(some);
+      takes |= takes >> 32 | takes << 32;
     }
     mc = max_halves(mc);
     const float mn = fmaxf(m, mc);
@@ -289,6 +304,15 @@ __global__ __launch_bounds__(kF32Threads, 2) void attn_f32_kernel(F32Params P) {
         for (int e = 0; e < 16; ++e)
           if (key_of(e) >= left) buf[e] = vecv(0.f);
       }
+      const bool apart = TOK != 0 && careful && takes != ~0ull;
+      float old[TOK != 0 ? 16 * DT : 1];
+      if (apart) {
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) old[16 * dt + e] = oacc[dt][e];
+        asm volatile("" : : "v"(&old[0]) : "memory");  // (in scratch memory, not in registers)
+      }
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
 #pragma unroll
@@ -297,11 +321,29 @@ __global__ __launch_bounds__(kF32Threads, 2) void attn_f32_kernel(F32Params P) {
         if (e % CE == CE - 1) load_chunk(tok_n, e / CE);
         __builtin_amdgcn_sched_barrier(0);
       }
+      if (apart && !(takes >> lane & 1)) {
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) oacc[dt][e] = old[16 * dt + e];
+      }
     }
     i = i_n;
     pos = pos_n;
     ns = ns_n;
     tok = tok_n;
+  }
+
+  if constexpr (TOK != 0) {
+    float z = 0.f;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) z = fmaf(oacc[dt][e], 0.f, z);  // NaN where a sum is not finite
+    if (!careful && __ballot(z != 0.f) != 0) {
+      careful = true;
+      goto again;
+    }
   }
 
   // ---- merge the waves' states: waves s..2s-1 into waves 0..s-1, s = 4, 2, 1

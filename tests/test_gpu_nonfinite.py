@@ -108,3 +108,31 @@ def test_fp32_infinite_last_value(head_dim):
                 tra.tra_token_attention(plan, q, k, v, full, cnt, cols, None, o)
             assert not o.isnan().any(), (call, h)
             assert torch.equal(o[0, 0] == float("inf"), want), (call, h)
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("mixed", [False, True])
+def test_fp32_token_value_out_of_reach(head_dim, mixed):
+    """Token-level call, a column of 8 blocks of 8 x 8, every block listed: an infinite
+    value in the last block reaches no query of short radius in the others, also where
+    one query among its 32 has the full radius (mixed) and gets it."""
+    import torch
+    import paper_2608_02504_amd as tra
+    plan = tra.Plan(tra.Config(1, 1, 1, 64, 8, head_dim, block=64, tile_h=8, tile_w=8, dtype="fp32"))
+    S, NB = plan.n_tokens, plan.n_blocks  # (raster order is the tile-major order here)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    q, k, v = (torch.randn(1, 1, S, head_dim, generator=g, device="cuda") for _ in range(3))
+    v[0, 0, S - 5, 3] = float("inf")
+    cnt = torch.full((1, 1, NB), NB, dtype=torch.int32, device="cuda")
+    cols = torch.arange(NB, dtype=torch.int32, device="cuda").expand(1, 1, NB, NB).contiguous()
+    rad = torch.full((1, 1, S), 2, dtype=torch.int32, device="cuda")
+    if mixed:
+        rad[0, 0, 5::32] = tra.TRA_RADIUS_FULL
+    o = torch.empty_like(q)
+    tra.tra_token_attention(plan, q, k, v, rad, cnt, cols, None, o)
+    far = o[0, 0, :S - 64]
+    inf = torch.zeros_like(far, dtype=torch.bool)
+    if mixed:
+        inf[5::32, 3] = True
+    assert not far.isnan().any()
+    assert torch.equal(far == float("inf"), inf)
