@@ -36,6 +36,7 @@
 // lse = m + log l.  The token-level variant (Eq. 16 with the token mask of Eq.
 // 15 inside the listed blocks) tests every (query, key) pair with the plan's
 // integer thresholds, as the block-mask kernel does.
+#include <algorithm>
 #include <cmath>
 
 #include "tra_internal.h"
@@ -64,6 +65,7 @@ struct F32Params {
   const int32_t* radius_sq;
   const int32_t* thr;  // [(n_cap + 1) * F], 2-D or 1-D thresholds per the plan
   int Nv, F, n_cap;
+  int first;  // the launch's first query tile (see launch_f32_d)
 };
 
 constexpr int kWaves = 8;
@@ -113,14 +115,14 @@ __global__ __launch_bounds__(kF32Threads, 2) void attn_f32_kernel(F32Params P) {
   __shared__ float sStat[kWaves / 2][3][kTile];
 
   const int subs = P.B / kTile;  // query tiles per row, key tiles per block
-  const int total = P.rows * subs;
   int idx = blockIdx.x;
   if (!(SPARSE && P.order)) {
     // workgroup b runs on XCD b mod 8: give each XCD a contiguous range of
     // query tiles, so that those in flight share a head's K and V in its L2
-    const int x = idx & 7, per = total / 8, rem = total % 8;
+    const int x = idx & 7, per = (int)gridDim.x / 8, rem = (int)gridDim.x % 8;
     idx = x * per + min(x, rem) + (idx >> 3);
   }
+  idx += P.first;
   int r = idx / subs;
   const int qsub = idx - r * subs;
   if (SPARSE && P.order) {
@@ -416,23 +418,32 @@ hipError_t launch_f32_d(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
               a.entropy, p.d_perm, p.d_coord, a.cnt, a.cols, a.order,
               a.sparse && p.cfg.block_layout == TRA_BLOCKS_TILES ? p.d_bcount : nullptr, p.S, p.NB, p.rows,
               p.cfg.block, 1.0f / sqrtf((float)D), a.radius_sq, one_d ? p.d_thr1 : p.d_thr, p.N,
-              p.cfg.frames, p.n_cap};
-  const dim3 grid(p.rows * (p.cfg.block / kTile)), block(kF32Threads);
+              p.cfg.frames, p.n_cap, 0};
+  // (a launch holds fewer than 2^32 threads: a plan of many short rows, all padding but
+  // a few tokens, has more query tiles than that)
+  constexpr int kMostTiles = 1 << 22;
+  const int tiles = p.rows * (p.cfg.block / kTile);
+  const dim3 block(kF32Threads);
   if (a.ev_start) (void)hipEventRecord(a.ev_start, s);
-  if (a.sparse && a.radius_sq && one_d)
-    hipLaunchKernelGGL((attn_f32_kernel<D, true, true, false, 2>), grid, block, 0, s, P);
-  else if (a.sparse && a.radius_sq)
-    hipLaunchKernelGGL((attn_f32_kernel<D, true, true, false, 1>), grid, block, 0, s, P);
-  else if (a.sparse)
-    hipLaunchKernelGGL((attn_f32_kernel<D, true, true, false>), grid, block, 0, s, P);
-  else if (a.entropy && a.o)
-    hipLaunchKernelGGL((attn_f32_kernel<D, false, true, true>), grid, block, 0, s, P);
-  else if (a.entropy)
-    hipLaunchKernelGGL((attn_f32_kernel<D, false, false, true>), grid, block, 0, s, P);
-  else
-    hipLaunchKernelGGL((attn_f32_kernel<D, false, true, false>), grid, block, 0, s, P);
+  for (P.first = 0; P.first < tiles; P.first += kMostTiles) {
+    const dim3 grid(std::min(tiles - P.first, kMostTiles));
+    if (a.sparse && a.radius_sq && one_d)
+      hipLaunchKernelGGL((attn_f32_kernel<D, true, true, false, 2>), grid, block, 0, s, P);
+    else if (a.sparse && a.radius_sq)
+      hipLaunchKernelGGL((attn_f32_kernel<D, true, true, false, 1>), grid, block, 0, s, P);
+    else if (a.sparse)
+      hipLaunchKernelGGL((attn_f32_kernel<D, true, true, false>), grid, block, 0, s, P);
+    else if (a.entropy && a.o)
+      hipLaunchKernelGGL((attn_f32_kernel<D, false, true, true>), grid, block, 0, s, P);
+    else if (a.entropy)
+      hipLaunchKernelGGL((attn_f32_kernel<D, false, false, true>), grid, block, 0, s, P);
+    else
+      hipLaunchKernelGGL((attn_f32_kernel<D, false, true, false>), grid, block, 0, s, P);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   if (a.ev_stop) (void)hipEventRecord(a.ev_stop, s);
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 }  // namespace

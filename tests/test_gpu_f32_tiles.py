@@ -46,3 +46,29 @@ def test_fp32_padded_blocks(shape):
         q, k, v = (synth.to_f64(a[0, h], "fp32") for a in (run.q_np, run.k_np, run.v_np))
         rows, o_ref = O.masked_attention_rows(q, k, v, tabs.perm, w.block, list(range(tabs.n_blocks)), M)
         assert np.abs(to_np_f64(run.O_sp[0, h])[rows] - o_ref).max() <= TOL_O_FP32
+
+
+@pytest.mark.parametrize("call", ["entropy", "sparse"])
+def test_fp32_more_tiles_than_a_launch_holds(call):
+    """2^21 + 2^10 one-token heads of 128-token blocks: 2^23 + 2^12 query tiles of 512
+    threads, more than the 2^32 threads of one launch.  A lone key's output is its
+    value and its entropy 0, whatever the score."""
+    import torch
+    import paper_2608_02504_amd as tra
+    n = (1 << 21) + (1 << 10)
+    assert n * 4 * 512 > 1 << 32
+    plan = tra.Plan(tra.Config(1 << 10, n >> 10, 1, 1, 1, 64, dtype="fp32"))
+    g = torch.Generator(device="cuda").manual_seed(1)
+    q, v = (torch.randn(1 << 10, n >> 10, 1, 64, generator=g, device="cuda") for _ in range(2))
+    o = torch.full_like(v, -1.0)
+    per = torch.full((1 << 10, n >> 10, 1), -1.0, device="cuda")
+    if call == "entropy":
+        tra.tra_entropy(plan, q, q, v, o, per)
+        assert (per == 0).all()
+    else:
+        cnt = torch.ones(1 << 10, n >> 10, 1, dtype=torch.int32, device="cuda")
+        cols = torch.zeros(1 << 10, n >> 10, 1, 1, dtype=torch.int32, device="cuda")
+        tra.tra_sparse_attention(plan, q, q, v, cnt, cols, None, o, per)
+        want = (q.double() ** 2).sum(-1) / 8
+        assert ((per.double() - want).abs() <= 1e-5 * want).all()
+    assert torch.equal(o, v)
