@@ -1933,9 +1933,18 @@ long long most_work(const tra_plan_s& p, const AttnArgs& a) {
   return (long long)p.rows * (has_units(p, a) ? (p.NB + kSplitMin - 1) / kSplitMin : 1);
 }
 
-// The pre-pass of a call whose work is cut for `grid` workgroups.
+// The attention kernel's launch result, its stop event recorded where it is timed.
+hipError_t attention_launched(const AttnArgs& a, hipStream_t s) {
+  const hipError_t e = hipGetLastError();
+  if (a.ev_stop) (void)hipEventRecord(a.ev_stop, s);
+  return e;
+}
+
+// The pre-pass of a call whose work is cut for `grid` workgroups.  Every kernel after
+// it reads what it wrote (queue counters, unit tables, copies): a caller launches
+// nothing more where it fails.
 template <int D>
-void launch_prep(const tra_plan_s& p, const AttnArgs& a, int grid, hipStream_t s, DenseSplit ds = {0, 1}) {
+hipError_t launch_prep(const tra_plan_s& p, const AttnArgs& a, int grid, hipStream_t s, DenseSplit ds = {0, 1}) {
   const bool units = has_units(p, a);
   const PlanArgs pa{units ? a.cnt : nullptr, a.order, p.rows, p.NB, grid, p.units_cap, p.splits_cap, p.slots_cap,
                     (int4*)p.d_units, (int4*)p.d_splits, p.d_unit_hdr, p.d_row_ctr, ds};
@@ -1951,6 +1960,7 @@ void launch_prep(const tra_plan_s& p, const AttnArgs& a, int grid, hipStream_t s
   };
   if (few_rows(p, a)) a.v ? launch(prep_kernel<D, true, true>) : launch(prep_kernel<D, false, true>);
   else a.v ? launch(prep_kernel<D, true, false>) : launch(prep_kernel<D, false, false>);
+  return hipGetLastError();
 }
 
 // The unit table of a call, NULL where its rows are its work.
@@ -1986,7 +1996,7 @@ DenseSplit dense_split(int rows, int NB, int cap) {
 }
 
 template <int D>
-void launch_merge(const tra_plan_s& p, const AttnArgs& a, long long splits, hipStream_t s) {
+hipError_t launch_merge(const tra_plan_s& p, const AttnArgs& a, long long splits, hipStream_t s) {
   const dim3 grid(std::max(1, (int)std::min<long long>(splits * (kBQ / kMergeQueries<D>), 16LL * p.n_cu)));
   if (a.lse)
     hipLaunchKernelGGL((merge_split_rows_kernel<D, true>), grid, dim3(256), 0, s, (const int4*)p.d_splits,
@@ -1994,44 +2004,44 @@ void launch_merge(const tra_plan_s& p, const AttnArgs& a, long long splits, hipS
   else
     hipLaunchKernelGGL((merge_split_rows_kernel<D, false>), grid, dim3(256), 0, s, (const int4*)p.d_splits,
                        p.d_unit_hdr, p.d_part, p.d_pstats, (uint16_t*)a.o, a.lse, p.d_perm, p.S, p.NB);
+  return hipGetLastError();
 }
 
 template <int D, bool SPARSE, bool LSE, bool CUT>
-void launch_k64_kernel(const tra_plan_s& p, const AttnArgs& a, int cap, DenseSplit ds, hipStream_t s) {
+hipError_t launch_k64_kernel(const tra_plan_s& p, const AttnArgs& a, int cap, DenseSplit ds, hipStream_t s) {
   const float scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)D));
   const size_t lds_bytes = SPARSE ? (size_t)p.NB * sizeof(int32_t) : 0;
   const int grid = (int)std::min<long long>(cap, most_work(p, a) + 8LL * ds.tail * (ds.pieces - 1));
-  launch_prep<D>(p, a, cap, s, ds);
+  const hipError_t e = launch_prep<D>(p, a, cap, s, ds);
+  if (e != hipSuccess) return e;
   if (a.ev_start) (void)hipEventRecord(a.ev_start, s);
   hipLaunchKernelGGL((attn_k64_kernel<D, SPARSE, LSE, CUT>), dim3(grid), dim3(kThreads), lds_bytes, s,
                      (const uint16_t*)a.q, p.d_kt, p.d_vt, (uint16_t*)a.o, a.lse, p.d_perm, a.cnt, a.cols, a.order,
                      p.cfg.block_layout == TRA_BLOCKS_TILES ? p.d_bcount : nullptr, unit_table(p, a), p.d_unit_hdr, ds,
                      p.S, p.n_pad, p.NB, p.rows, scale_log2, p.d_row_ctr, p.d_part, p.d_pstats);
-  if (a.ev_stop) (void)hipEventRecord(a.ev_stop, s);
+  return attention_launched(a, s);
 }
 
 template <int D, bool SPARSE, bool LSE>
-void launch_k64_lse(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
+hipError_t launch_k64_lse(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
   const size_t lds_bytes = SPARSE ? (size_t)p.NB * sizeof(int32_t) : 0;
   if constexpr (!SPARSE) {
     const int cap = resident_grid(attn_k64_kernel<D, false, LSE, true>, 0, p, INT_MAX);
     const DenseSplit ds = dense_split(p.rows, p.NB, cap);
     if (ds.tail > 0 && 8 * ds.tail * ds.pieces <= p.dense_slots) {  // (always within the plan's bound)
-      launch_k64_kernel<D, false, LSE, true>(p, a, cap, ds, s);
-      launch_merge<D>(p, a, 8LL * ds.tail, s);
-      return;
+      const hipError_t e = launch_k64_kernel<D, false, LSE, true>(p, a, cap, ds, s);
+      return e != hipSuccess ? e : launch_merge<D>(p, a, 8LL * ds.tail, s);
     }
   }
   const int cap = std::min(resident_grid(attn_k64_kernel<D, SPARSE, LSE>, lds_bytes, p, INT_MAX),
                            SPARSE ? p.split_wg_cap : INT_MAX);
-  launch_k64_kernel<D, SPARSE, LSE, false>(p, a, cap, DenseSplit{0, 1}, s);
-  if (has_units(p, a)) launch_merge<D>(p, a, p.splits_cap, s);
+  const hipError_t e = launch_k64_kernel<D, SPARSE, LSE, false>(p, a, cap, DenseSplit{0, 1}, s);
+  return e != hipSuccess || !has_units(p, a) ? e : launch_merge<D>(p, a, p.splits_cap, s);
 }
 
 template <int D, bool SPARSE>
-void launch_k64(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
-  if (a.lse) launch_k64_lse<D, SPARSE, true>(p, a, s);
-  else launch_k64_lse<D, SPARSE, false>(p, a, s);
+hipError_t launch_k64(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
+  return a.lse ? launch_k64_lse<D, SPARSE, true>(p, a, s) : launch_k64_lse<D, SPARSE, false>(p, a, s);
 }
 
 // ------------------------------------------------------------ fused entropy + dense output
@@ -2267,15 +2277,16 @@ __global__ __launch_bounds__(kFusedThreads, 1) void attn_fused_kernel(
 }
 
 template <int D>
-void launch_fused_entropy_output(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
+hipError_t launch_fused_entropy_output(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
   const float scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)D));
   const int grid = resident_grid(attn_fused_kernel<D>, 0, p, p.rows, kFusedThreads);
-  launch_prep<D>(p, a, grid, s);
+  const hipError_t e = launch_prep<D>(p, a, grid, s);
+  if (e != hipSuccess) return e;
   if (a.ev_start) (void)hipEventRecord(a.ev_start, s);
   hipLaunchKernelGGL((attn_fused_kernel<D>), dim3(grid), dim3(kFusedThreads), 0, s, (const uint16_t*)a.q,
                      p.d_kt, p.d_vt, (uint16_t*)a.o, a.entropy, p.d_perm, p.S, p.n_pad, p.NB, p.rows,
                      scale_log2, p.d_row_ctr);
-  if (a.ev_stop) (void)hipEventRecord(a.ev_stop, s);
+  return attention_launched(a, s);
 }
 
 // ------------------------------------------------------------ calls of few rows
@@ -2513,20 +2524,21 @@ __global__ __launch_bounds__(kSmallThreads, 2) void attn_small_kernel(
 }
 
 template <int D, bool SPARSE, bool PV, bool ENT>
-void launch_small(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
+hipError_t launch_small(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
   const float scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)D));
-  launch_prep<D>(p, a, 1, s);
+  const hipError_t e = launch_prep<D>(p, a, 1, s);
+  if (e != hipSuccess) return e;
   if (a.ev_start) (void)hipEventRecord(a.ev_start, s);
   hipLaunchKernelGGL((attn_small_kernel<D, SPARSE, PV, ENT>), dim3(p.rows * (kBQ / kSmallQ)), dim3(kSmallThreads),
                      SPARSE ? (size_t)p.NB * sizeof(int32_t) : 0, s, (const uint16_t*)a.q, p.d_kt, p.d_vt,
                      (uint16_t*)a.o, a.lse, a.entropy, p.d_perm, a.cnt, a.cols, a.order,
                      SPARSE && p.cfg.block_layout == TRA_BLOCKS_TILES ? p.d_bcount : nullptr, p.S, p.n_pad, p.NB,
                      p.rows, scale_log2);
-  if (a.ev_stop) (void)hipEventRecord(a.ev_stop, s);
+  return attention_launched(a, s);
 }
 
 template <int D, bool SPARSE, bool PV, bool ENT, int TOK = 0>
-void launch_variant(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
+hipError_t launch_variant(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
   const float scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)D));
   size_t lds_bytes = SPARSE ? (size_t)((p.NB + 3) & ~3) * sizeof(int32_t) : 0;
   if (TOK != 0) lds_bytes += (size_t)kBQ * p.cfg.frames * sizeof(uint16_t);
@@ -2535,32 +2547,32 @@ void launch_variant(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
   const int cap = std::min(resident_grid(attn_bf16_kernel<D, SPARSE, PV, ENT, 2, TOK>, lds_bytes, p, INT_MAX),
                            SPARSE ? p.split_wg_cap : INT_MAX);
   const int grid = (int)std::min<long long>(cap, most_work(p, a));
-  launch_prep<D>(p, a, cap, s);
+  hipError_t e = launch_prep<D>(p, a, cap, s);
+  if (e != hipSuccess) return e;
   if (a.ev_start) (void)hipEventRecord(a.ev_start, s);
   hipLaunchKernelGGL((attn_bf16_kernel<D, SPARSE, PV, ENT, 2, TOK>), dim3(grid), dim3(kThreads), lds_bytes, s,
                      (const uint16_t*)a.q, p.d_kt, p.d_vt, (uint16_t*)a.o, a.lse, a.entropy, p.d_perm, a.cnt,
                      a.cols, a.order, unit_table(p, a), p.d_unit_hdr, p.S, p.n_pad, p.NB, p.rows, scale_log2, tk,
                      p.d_row_ctr, p.d_part, p.d_pstats);
-  if (a.ev_stop) (void)hipEventRecord(a.ev_stop, s);
-  if (has_units(p, a)) launch_merge<D>(p, a, p.splits_cap, s);
+  e = attention_launched(a, s);
+  return e != hipSuccess || !has_units(p, a) ? e : launch_merge<D>(p, a, p.splits_cap, s);
 }
 
 template <int D>
 hipError_t launch_bf16_d(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
   const bool text = p.S > p.N;
-  if (a.sparse && a.radius_sq && p.cfg.distance == TRA_DIST_1D && text) launch_variant<D, true, true, false, 6>(p, a, s);
-  else if (a.sparse && a.radius_sq && p.cfg.distance == TRA_DIST_1D) launch_variant<D, true, true, false, 2>(p, a, s);
-  else if (a.sparse && a.radius_sq && text) launch_variant<D, true, true, false, 5>(p, a, s);
-  else if (a.sparse && a.radius_sq) launch_variant<D, true, true, false, 1>(p, a, s);
-  else if (few_rows(p, a) && a.sparse) launch_small<D, true, true, false>(p, a, s);
-  else if (few_rows(p, a) && a.entropy && a.o) launch_small<D, false, true, true>(p, a, s);
-  else if (few_rows(p, a) && a.entropy) launch_small<D, false, false, true>(p, a, s);
-  else if (few_rows(p, a)) launch_small<D, false, true, false>(p, a, s);
-  else if (a.sparse) launch_k64<D, true>(p, a, s);
-  else if (a.entropy && a.o) launch_fused_entropy_output<D>(p, a, s);
-  else if (a.entropy) launch_variant<D, false, false, true>(p, a, s);
-  else launch_k64<D, false>(p, a, s);
-  return hipGetLastError();
+  if (a.sparse && a.radius_sq && p.cfg.distance == TRA_DIST_1D && text) return launch_variant<D, true, true, false, 6>(p, a, s);
+  if (a.sparse && a.radius_sq && p.cfg.distance == TRA_DIST_1D) return launch_variant<D, true, true, false, 2>(p, a, s);
+  if (a.sparse && a.radius_sq && text) return launch_variant<D, true, true, false, 5>(p, a, s);
+  if (a.sparse && a.radius_sq) return launch_variant<D, true, true, false, 1>(p, a, s);
+  if (few_rows(p, a) && a.sparse) return launch_small<D, true, true, false>(p, a, s);
+  if (few_rows(p, a) && a.entropy && a.o) return launch_small<D, false, true, true>(p, a, s);
+  if (few_rows(p, a) && a.entropy) return launch_small<D, false, false, true>(p, a, s);
+  if (few_rows(p, a)) return launch_small<D, false, true, false>(p, a, s);
+  if (a.sparse) return launch_k64<D, true>(p, a, s);
+  if (a.entropy && a.o) return launch_fused_entropy_output<D>(p, a, s);
+  if (a.entropy) return launch_variant<D, false, false, true>(p, a, s);
+  return launch_k64<D, false>(p, a, s);
 }
 
 }  // namespace
