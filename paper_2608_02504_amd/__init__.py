@@ -314,10 +314,14 @@ def _workspace(plan: Plan, handle: int, workspace):
     ws = plan._ws.get(handle)
     if ws is None:
         import torch
-        ws = torch.empty(plan.ws_bytes, dtype=torch.uint8, device="cuda")
-        if handle != _current_stream():
-            # freed only when the plan closes: keep it until that stream's work is done
-            ws.record_stream(torch.cuda.ExternalStream(handle))
+        if handle == _current_stream():
+            ws = torch.empty(plan.ws_bytes, dtype=torch.uint8, device="cuda")
+        else:
+            # from that stream's own memory: a block that another stream has just given
+            # back may still be in use there
+            own = torch.cuda.ExternalStream(handle) if handle else torch.cuda.default_stream()
+            with torch.cuda.stream(own):
+                ws = torch.empty(plan.ws_bytes, dtype=torch.uint8, device="cuda")
         plan._ws[handle] = ws
     return ws.data_ptr(), plan.ws_bytes
 

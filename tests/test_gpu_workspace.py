@@ -66,6 +66,34 @@ def test_plan_shared_by_two_streams():
     log("one plan on two concurrent streams: every output equals the sequential calls")
 
 
+@pytest.mark.parametrize("as_handle", [False, True])
+def test_workspace_of_a_named_stream(as_handle):
+    """stream= another than the current one: the workspace is not a block that the
+    current stream has just given back (its kernels may still be writing it), and
+    with the current stream named 0 (the default) while a side stream is current."""
+    _gpu()
+    import torch
+    import paper_2608_02504_amd as tra
+    run = Run(W, radius_override=40)
+    side = torch.cuda.Stream()
+    for call, current in ((side, torch.cuda.default_stream()), (torch.cuda.default_stream(), side)):
+        plan = tra.Plan(run.cfg)
+        o = torch.empty_like(run.q)
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        with torch.cuda.stream(current):
+            x = torch.full((plan.ws_bytes,), 1, dtype=torch.uint8, device="cuda")
+            given_back = x.data_ptr()
+            del x
+            tra.tra_sparse_attention(plan, run.q, run.k, run.v, run.cnt, run.cols, run.order, o,
+                                     stream=call.cuda_stream if as_handle else call)
+            assert plan._ws[call.cuda_stream].data_ptr() != given_back
+            # the block is still the current stream's to use
+            assert torch.empty(plan.ws_bytes, dtype=torch.uint8, device="cuda").data_ptr() == given_back
+        torch.cuda.synchronize()
+        assert torch.equal(o, run.O_sp)
+
+
 def test_explicit_workspace_and_checks():
     """A caller's workspace of exactly tra_workspace_size bytes gives the same
     output; a smaller, misaligned or NULL one is refused with
