@@ -17,11 +17,14 @@
 // A row of the table is monotone, and what a search in it costs is the cache
 // lines it touches: a bisection over 8,178 entries touches about nine (3.3 GB for
 // 3.0 million queries, which took 0.44 ms).  Each row therefore has a small index,
-// the counts that end every 32 entries (level B) and every 512 (level A), and a
-// query reads one 64-byte run of A and of B and one 128-byte line of the row, each
-// as independent 16-byte loads, counting the entries below K_hat.  Workgroups walk
+// the counts that end every 32 entries (level B) and every 512 (level A).  A query
+// takes the 64-byte run of A that holds K_hat (by bisection where A has several: n_cap
+// >= 8,192), then one run of B and one 128-byte line of the row, counting in each the
+// entries below K_hat, B and the line by independent 16-byte loads.  Workgroups walk
 // the heads of one run of tokens in turn, so that those on one XCD share A and B
-// in its L2.  75,600 tokens x 40 heads: 443 -> 96 us.
+// in its L2.  75,600 tokens x 40 heads: 443 -> 96 us.  A's runs read one after another
+// instead: 9.8 us against 5.6 at 1 x 512 x 2 x 64 heads (n_cap 261,122, 32 runs), 5.8
+// against 6.4 at 1 x 128 x 128 x 8 heads (4 runs).
 // Plans whose table would exceed a size limit keep only C(n_cap) per position and
 // count the other radii on the fly (exact lattice counts, row by row), by
 // bisection.  Counts are exact integers either way.
@@ -93,7 +96,7 @@ __global__ __launch_bounds__(256) void disk_table_kernel(int32_t* __restrict__ d
 
 // Layout of the count table: rows of `row` ints (n_cap + 1 padded to whole
 // 32-entry lines with C(n_cap)), each with `na` + `nb` ints of index.
-constexpr int kLine = 32, kGroup = 16;
+constexpr int kLine = 32, kGroup = 16, kRun = 16;
 struct CountLayout {
   int row, na, nb;
   __host__ __device__ explicit CountLayout(int n_cap) {
@@ -199,8 +202,15 @@ __global__ __launch_bounds__(256) void budget_radius_kernel(
     const int fq = min(f, F - 1 - f), xq = min(x, H - 1 - x), yq = min(y, W - 1 - y);
     const size_t p = (size_t)(fq * hh + xq) * wh + yq;
     const int32_t* A = cidx + p * L.index();
-    int g = 0;
-    for (int a = 0; a < L.na; a += 4) {
+    int run = 0;  // the first run of A whose end reaches khat (the last one may not)
+    for (int n = (L.na + kRun - 1) / kRun; n > 1;) {
+      const int h = n / 2;
+      const bool past = A[(run + h) * kRun - 1] < khat;
+      run += past ? h : 0;
+      n = past ? n - h : h;
+    }
+    int g = run * kRun;
+    for (int a = g; a < min(L.na, run * kRun + kRun); a += 4) {
       const int c = count_below<1>(A + a, khat);
       g += c;
       if (c < 4) break;

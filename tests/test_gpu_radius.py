@@ -1,5 +1,5 @@
 """The radius search through the count table's index at row lengths around its
-line (32) and group (512) sizes, budgets from 1 past the largest count, against
+line (32), group (512) and run (8,192) sizes, budgets from 1 past the largest count, against
 the oracle's search, integer for integer."""
 import math
 
@@ -11,9 +11,10 @@ import oracle as O
 pytestmark = pytest.mark.gpu
 
 
-# n_cap = (H-1)^2 + (W-1)^2: 0, 26, 32, 128, 493, 512, 545, 8,177
+# n_cap = (H-1)^2 + (W-1)^2: 0, 26, 32, 128, 493, 512, 545, 8,177; 8,200 (two runs of the index's first
+# level), 16,385 (three), 39,602 (five)
 @pytest.mark.parametrize("grid", [(3, 1, 1, 200), (5, 2, 6, 9), (4, 5, 5, 0), (3, 9, 9, 0), (2, 4, 23, 3), (3, 17, 17, 0),
-                                  (2, 17, 18, 0), (3, 45, 80, 5)], ids=str)
+                                  (2, 17, 18, 0), (3, 45, 80, 5), (2, 91, 11, 3), (2, 129, 2, 0), (1, 2, 200, 7)], ids=str)
 @pytest.mark.parametrize("gamma", [0.0, 0.6])
 def test_radius_index(grid, gamma):
     import torch
