@@ -1906,15 +1906,19 @@ int k64_sparse_grid_cap_d(const tra_plan_s& p) {
 }
 
 // Calls that the key-splitting kernel takes (attn_small_kernel): its 4 rows
-// workgroups of 8 waves, one per CU at head_dim 128 (210 registers) and two at 64, fill
-// two rounds of the GPU at most (three at head_dim 64), and one for the fused call,
-// whose own kernel splits the keys in two already.  Measured with every block kept,
+// workgroups of 8 waves, one per CU at head_dim 128 (up to 232 registers) and two at 64
+// (128), fill two rounds of 256 CUs at most, at head_dim 64 three counted one a CU
+// (one and a half of two).  The fused call's own kernel splits the keys in two already:
+// one round at head_dim 128, three as the others at 64.  Measured with every block kept,
 // microseconds of a call without and with it (pre-pass included), 256 CUs:
 //   head_dim 128  8 rows of 8 blocks: dense 31 / 18, fused 27 / 18, entropy 20 / 19;
 //     64 of 16: 52 / 25, 41 / 25, 31 / 17; 128 of 16: 56 / 44, 45 / 46, 34 / 25; 128 of
 //     128: 313 / 198, 204 / 199, 178 / 118; 192 of 16: 63 / 62, 53 / 62; 256 of 16: 64 / 80
 //   head_dim 64  128 rows of 16: 45 / 25, 36 / 26; 192 of 64: 138 / 88, 100 / 95;
 //     256 of 128: 259 / 210, 197 / 220; 512 of 32: 109 / 122
+// and block-sparse calls of short lists (head_dim 128, 64), of rows of 16 blocks at 9 %:
+//   16 rows 48 / 16, 43 / 12; 64 rows 50 / 18, 44 / 13; 128 rows 52 / 30, 45 / 17; 128
+//   rows of 128 blocks at 9 % 74 / 46, 65 / 31, at 30 % 205 / 120, 172 / 74.
 bool few_rows(const tra_plan_s& p, const AttnArgs& a) {
   if (a.radius_sq) return false;  // token level: its own kernel
   const int rounds = a.entropy && a.o ? (p.cfg.head_dim == 64 ? 3 : 1) : p.cfg.head_dim == 64 ? 3 : 2;
@@ -2304,8 +2308,10 @@ hipError_t launch_fused_entropy_output(const tra_plan_s& p, const AttnArgs& a, h
 // many (few_rows has the measurements).
 // The split depends on a row's valid entries only, so a list that keeps every block
 // gives the dense call's result bit for bit.
+// (At head_dim 64 held to 128 registers, which two workgroups a CU need: at 130 the
+// block-sparse call of 128 rows of 16 blocks took 19.7 us, now 16.7.)
 template <int D, bool SPARSE, bool PV, bool ENT>
-__global__ __launch_bounds__(kSmallThreads, 2) void attn_small_kernel(
+__global__ __launch_bounds__(kSmallThreads, D == 64 ? 4 : 2) void attn_small_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ ktile, const uint16_t* __restrict__ vtile,
     uint16_t* __restrict__ o, float* __restrict__ lse, float* __restrict__ entropy,
     const int32_t* __restrict__ perm, const int32_t* __restrict__ cnt, const int32_t* __restrict__ cols,
@@ -2338,12 +2344,14 @@ __global__ __launch_bounds__(kSmallThreads, 2) void attn_small_kernel(
   const int qtok = perm[u * kBQ + qsub * kSmallQ + col];  // -1 at a padding position
   const bool qvalid = qtok >= 0;
   if (__ballot(qvalid) == 0) return;  // (every wave holds the same 32 queries)
-  const uint4 zero4 = make_uint4(0, 0, 0, 0);
   bf16x8 qf[KK];
   {
     const uint4* src = (const uint4*)(q + ((size_t)bh * N + max(qtok, 0)) * D);
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) qf[kk] = __builtin_bit_cast(bf16x8, qvalid ? src[2 * kk + half] : zero4);
+    for (int kk = 0; kk < KK; ++kk) {
+      const uint4 x = qvalid ? src[2 * kk + half] : make_uint4(0, 0, 0, 0);
+      qf[kk] = __builtin_bit_cast(bf16x8, x);
+    }
   }
   int count = NB;
   if constexpr (SPARSE) {

@@ -127,3 +127,30 @@ def test_no_scalar_stores_or_packed_fp32(assembly):
         for kname, lines in _kernels(text):
             for t in lines:
                 assert not banned.match(t), f"{fname}:{kname}: '{t}'"
+
+
+def _metadata(text):
+    """{kernel: {field: int}} of a source's code object metadata."""
+    out = {}
+    for entry in re.split(r"\n  - ", text[text.index("amdhsa.kernels:"):])[1:]:
+        fields = dict(re.findall(r"\.(\w+):\s+(\S+)", entry))
+        if "vgpr_count" in fields:
+            out[fields["name"]] = {k: int(v) for k, v in fields.items() if v.isdigit()}
+    return out
+
+
+def test_key_splitting_kernel_registers(assembly):
+    """attn_small_kernel is bound by latency: nothing of it goes through scratch
+    memory, and at head_dim 64 two workgroups of 8 waves fit a CU (four waves a SIMD,
+    128 registers each), as its dispatch rule counts on."""
+    kernels = {n: f for n, f in _metadata(assembly["attn_bf16.hip"]).items() if "attn_small_kernel" in n}
+    assert len(kernels) == 8
+    for name, f in kernels.items():
+        assert f["private_segment_fixed_size"] == 0 and f["vgpr_spill_count"] == 0, name
+        assert f["vgpr_count"] <= (128 if "ILi64E" in name else 256), name
+        if "ILi64E" in name:  # and their LDS, with a list of 4,096 entries (160 KB a CU)
+            assert 2 * (f["group_segment_fixed_size"] + 4 * 4096) <= 160 * 1024, name
+    for fname, text in assembly.items():
+        for kname, lines in _kernels(text):
+            if "attn_small_kernel" in kname:
+                assert not [t for t in lines if t.startswith(("scratch_", "flat_"))], kname
