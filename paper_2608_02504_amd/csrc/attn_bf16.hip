@@ -476,6 +476,21 @@ __device__ __forceinline__ void token_mask_mfma(f32x16 (&s)[4], const lds_u8* __
   }
 }
 
+// Next position of queue qd (thread 0 of a workgroup only): a workgroup's first claim
+// (steal < 0) is its rank among the workgroups whose home the queue is, without the
+// counter, the others follow them.  Workgroups are placed one a CU before the second
+// round, so a call of fewer work items than workgroups runs them on as many CUs as it
+// can; taken by whoever asks first, several landed on one CU while others had none
+// (4 heads x 110 blocks at 30 %, head_dim 64, 440 rows for 1,024 workgroups: 181 us,
+// now 147).
+__device__ __forceinline__ int claim(int32_t* ctr, int qd, int& steal) {
+  if (steal < 0) {
+    steal = 0;
+    return (int)blockIdx.x >> 3;
+  }
+  return ((int)gridDim.x - qd + 7) / 8 + atomicAdd(&ctr[qd * 16], 1);
+}
+
 // Row queue of the dense, entropy and fused kernels (thread 0 of a workgroup
 // only).  The rows are split into 8 contiguous ranges, one per XCD (the
 // workgroup with index b runs on XCD b mod 8), each drained through its own
@@ -483,13 +498,13 @@ __device__ __forceinline__ void token_mask_mfma(f32x16 (&s)[4], const lds_u8* __
 // head, which share most key tiles in its L2.  A workgroup whose range is
 // drained takes rows from the next ranges in turn, so an XCD that runs at a
 // higher clock ends up doing more rows.  Returns -1 once all is drained.
-// ctr: kRowCounters ints, zero before the launch; counter x at ctr[16 x].
+// ctr: kRowCounters ints, zero before the launch; counter x at ctr[16 x].  steal starts at -1.
 __device__ __forceinline__ int next_row(int32_t* ctr, int rows, int xcd, int& steal) {
   const int per = rows / 8, rem = rows % 8;
   while (steal < 8) {
-    const int qd = (xcd + steal) & 7;
+    const int qd = (xcd + max(steal, 0)) & 7;
     const int beg = qd * per + min(qd, rem), n = per + (qd < rem ? 1 : 0);
-    const int k = atomicAdd(&ctr[qd * 16], 1);
+    const int k = claim(ctr, qd, steal);
     if (k < n) return beg + k;
     ++steal;
   }
@@ -502,16 +517,47 @@ struct DenseSplit {
   int tail, pieces;
 };
 
+// Where a persistent kernel's work comes from and its pieces go.  Work of a
+// block-sparse or token-level call: the units of the work-unit table (see plan_units),
+// or, on plans whose rows are never cut (units NULL), the rows.  The kernel's first
+// argument, read where it is used (queue_args): held in registers through the tile
+// loop its pointers spilled up to 13 scalar registers and a vector one.
+struct QueueArgs {
+  const int32_t* cnt;    // [rows] list lengths
+  const int32_t* order;  // the caller's row order, or NULL
+  const int4* units;
+  const int32_t* hdr;
+  int32_t* ctr;          // the queue counters
+  float* part;           // partial results of pieces
+  float* pstats;
+  int rows, NB;
+  DenseSplit dense;
+};
+typedef const __attribute__((address_space(4))) QueueArgs* QueuePtr;
+
+__device__ __forceinline__ QueuePtr queue_args() {
+  QueuePtr p = (QueuePtr)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));  // (a load through it is not moved above this)
+  return p;
+}
+// A table that the kernel only reads, through the scalar cache.
+template <typename T>
+__device__ __forceinline__ const __attribute__((address_space(4))) T* table(const T* p) {
+  return (const __attribute__((address_space(4))) T*)p;
+}
+
 // The dense call's queue: as next_row, with the cut rows last, piece-major (piece 0
 // of every cut row, then piece 1, ...).  Returns {row, first key block, end, partial
 // slot or -1}; row -1 once all is drained.
-__device__ __forceinline__ int4 next_dense(int32_t* ctr, int rows, int NB, const DenseSplit& ds, int xcd,
-                                           int& steal) {
+__device__ __forceinline__ int4 next_dense(QueuePtr a, int xcd, int& steal) {
+  int32_t* ctr = a->ctr;
+  const int rows = a->rows, NB = a->NB;
+  const DenseSplit ds{a->dense.tail, a->dense.pieces};
   const int per = rows / 8, rem = rows % 8;
   while (steal < 8) {
-    const int qd = (xcd + steal) & 7;
+    const int qd = (xcd + max(steal, 0)) & 7;
     const int beg = qd * per + min(qd, rem), whole = per + (qd < rem ? 1 : 0) - ds.tail;
-    const int k = atomicAdd(&ctr[qd * 16], 1);
+    const int k = claim(ctr, qd, steal);
     if (k < whole) return make_int4(beg + k, 0, NB, -1);
     const int j = k - whole;
     if (j < ds.tail * ds.pieces) {
@@ -524,34 +570,23 @@ __device__ __forceinline__ int4 next_dense(int32_t* ctr, int rows, int NB, const
   return make_int4(-1, 0, 0, -1);
 }
 
-// Work of a block-sparse or token-level call: the units of the work-unit table
-// (see plan_units), or, on plans whose rows are never cut (units NULL), the rows.
-// (The kernels take the pointers as __restrict__ arguments of their own, which
-// lets the compiler read the tables through the scalar cache: as members of one
-// struct argument they cost 2-4 % of a 480p call in vector loads per claim.)
-struct WorkArgs {
-  const int32_t* cnt;    // [rows] list lengths
-  const int32_t* order;  // the caller's row order, or NULL
-  const int4* units;
-  const int32_t* hdr;
-  int rows, NB;
-};
-
-// Queue of that work (thread 0 of a workgroup only).  With the caller's order,
+// Queue of a block-sparse or token-level call (thread 0 of a workgroup only).  With the caller's order,
 // one counter walks the table (or the order); otherwise XCD x drains its segment
 // [seg[x], seg[x + 1]) of the table (or of the rows), then takes work from the
 // other segments in turn, as next_row.  Returns -1 once all is drained.
-__device__ __forceinline__ int next_work(int32_t* ctr, const WorkArgs& a, int xcd, int& steal) {
-  if (a.order) {
-    const int k = atomicAdd(&ctr[0], 1);
-    return k < (a.units ? a.hdr[0] : a.rows) ? k : -1;
+__device__ __forceinline__ int next_work(QueuePtr a, int xcd, int& steal) {
+  int32_t* ctr = a->ctr;
+  const auto* hdr = table(a->hdr);
+  if (a->order) {
+    const int k = steal < 0 ? (int)blockIdx.x : (int)gridDim.x + atomicAdd(&ctr[0], 1);
+    steal = 0;
+    return k < (a->units ? hdr[0] : a->rows) ? k : -1;
   }
-  if (!a.units) return next_row(ctr, a.rows, xcd, steal);
-  const int32_t* seg = a.hdr + 4;
+  if (!a->units) return next_row(ctr, a->rows, xcd, steal);
   while (steal < 8) {
-    const int qd = (xcd + steal) & 7;
-    const int beg = seg[qd], cnt = seg[qd + 1] - beg;
-    const int k = atomicAdd(&ctr[qd * 16], 1);
+    const int qd = __builtin_amdgcn_readfirstlane((xcd + max(steal, 0)) & 7);
+    const int beg = hdr[4 + qd], cnt = hdr[5 + qd] - beg;
+    const int k = claim(ctr, qd, steal);
     if (k < cnt) return beg + k;
     ++steal;
   }
@@ -560,17 +595,15 @@ __device__ __forceinline__ int next_work(int32_t* ctr, const WorkArgs& a, int xc
 
 // Work item w as {row, list begin, list end, partial slot or -1}; row -1: nothing
 // to do (a placeholder unit, or an order entry outside [0, rows)).
-// (The same in every lane: kept in scalar registers.)
-__device__ __forceinline__ int4 work_at(const WorkArgs& a, int w) {
-  int4 un = make_int4(-1, 0, 0, -1);
-  if (a.units) {
-    un = a.units[w];
-  } else {
-    const int r = a.order ? a.order[w] : w;
-    if (r >= 0 && r < a.rows) un = make_int4(r, 0, min(max(a.cnt[r], 0), a.NB), -1);
+// (The same in every lane: w and the result are in scalar registers.)
+__device__ __forceinline__ int4 work_at(QueuePtr a, int w) {
+  if (a->units) {
+    const auto* un = table((const int*)(a->units + w));
+    return make_int4(un[0], un[1], un[2], un[3]);
   }
-  return make_int4(__builtin_amdgcn_readfirstlane(un.x), __builtin_amdgcn_readfirstlane(un.y),
-                   __builtin_amdgcn_readfirstlane(un.z), __builtin_amdgcn_readfirstlane(un.w));
+  const int r = a->order ? table(a->order)[w] : w;
+  if (r < 0 || r >= a->rows) return make_int4(-1, 0, 0, -1);
+  return make_int4(r, 0, min(max(table(a->cnt)[r], 0), a->NB), -1);
 }
 
 // ------------------------------------------------------------ softmax and copy helpers
@@ -735,9 +768,9 @@ __device__ __forceinline__ void exp_pairs(f32x16 (&s)[4], float c, float m, floa
 // unnormalised, [slot][query][D], and its running max and sums.
 template <int D>
 __device__ __forceinline__ void write_partial(const f32x16 (&oacc)[Geo<D>::D_TILES], float m, float lr_tot,
-                                              float l_tot, int slot, int qi, int half, float* __restrict__ part,
-                                              float* __restrict__ pstats) {
-  float* po = part + ((size_t)slot * kBQ + qi) * D;
+                                              float l_tot, int slot, int qi, int half) {
+  const QueuePtr a = queue_args();
+  float* po = a->part + ((size_t)slot * kBQ + qi) * D;
 #pragma unroll
   for (int dt = 0; dt < Geo<D>::D_TILES; ++dt)
 #pragma unroll
@@ -745,7 +778,7 @@ __device__ __forceinline__ void write_partial(const f32x16 (&oacc)[Geo<D>::D_TIL
       *(float4*)(po + dt * 32 + 8 * g + 4 * half) =
           make_float4(oacc[dt][4 * g], oacc[dt][4 * g + 1], oacc[dt][4 * g + 2], oacc[dt][4 * g + 3]);
   if (half == 0) {
-    float* ps = pstats + (size_t)slot * 3 * kBQ;
+    float* ps = a->pstats + (size_t)slot * 3 * kBQ;
     ps[qi] = m;
     ps[kBQ + qi] = lr_tot;
     ps[2 * kBQ + qi] = l_tot;
@@ -767,8 +800,7 @@ __device__ __forceinline__ void bf16_row(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ ktile,
     const uint16_t* __restrict__ vtile, uint16_t* __restrict__ o, float* __restrict__ lse,
     float* __restrict__ entropy, const int32_t* __restrict__ perm, const int32_t* __restrict__ cols, int N,
-    int n_pad, int NB, float scale_log2, const TokArgs& tk, float* __restrict__ part,
-    float* __restrict__ pstats) {
+    int n_pad, int NB, float scale_log2, const TokArgs& tk) {
   using G = Geo<D>;
   uint16_t* thrq = (uint16_t*)(smemCols + ((NB + 3) & ~3));
   const int bh = r / NB, u = r - bh * NB;
@@ -1007,7 +1039,7 @@ __device__ __forceinline__ void bf16_row(
   const float lr_tot = PV ? sum_halves(st.lr) : 0.f;
   if constexpr (SPARSE && PV) {
     if (slot >= 0) {
-      write_partial<D>(oacc, st.m, lr_tot, l_tot, slot, wave * 32 + col, half, part, pstats);
+      write_partial<D>(oacc, st.m, lr_tot, l_tot, slot, wave * 32 + col, half);
       return;
     }
   }
@@ -1042,24 +1074,22 @@ __device__ __forceinline__ void bf16_row(
 // after its list is staged, orders the next s_row write after every wave's read).
 template <int D, bool SPARSE, bool PV, bool ENT, int OCC, int TOK = 0>
 __global__ __launch_bounds__(kThreads, OCC) void attn_bf16_kernel(
-    const uint16_t* __restrict__ q, const uint16_t* __restrict__ ktile,
+    QueueArgs, const uint16_t* __restrict__ q, const uint16_t* __restrict__ ktile,
     const uint16_t* __restrict__ vtile, uint16_t* __restrict__ o, float* __restrict__ lse,
-    float* __restrict__ entropy, const int32_t* __restrict__ perm, const int32_t* __restrict__ cnt,
-    const int32_t* __restrict__ cols, const int32_t* __restrict__ order, const int4* __restrict__ units,
-    const int32_t* __restrict__ unit_hdr, int N, int n_pad, int NB, int rows, float scale_log2, TokArgs tk,
-    int32_t* __restrict__ ctr, float* __restrict__ part, float* __restrict__ pstats) {
-  const WorkArgs wk{cnt, order, units, unit_hdr, rows, NB};
+    float* __restrict__ entropy, const int32_t* __restrict__ perm, const int32_t* __restrict__ cols, int N, int n_pad,
+    int NB, float scale_log2, TokArgs tk) {
   constexpr int TILE = kBK * D * 2;
   __shared__ __attribute__((aligned(1024))) uint8_t smemK[TILE];
   __shared__ __attribute__((aligned(1024))) uint8_t smemV[PV ? TILE : 16];
   __shared__ __attribute__((aligned(16))) uint8_t smemKinfo[(TOK & 3) == 1 ? 2 * kBK * kKeyFeat * 2 : TOK ? 2 * 1024 : 16];
   extern __shared__ int32_t smemCols[];
   __shared__ int s_row, s_steal;  // thread 0's queue state lives in LDS, not in a register
-  if (threadIdx.x == 0) s_steal = 0;
+  if (threadIdx.x == 0) s_steal = -1;
   for (;;) {
     if (threadIdx.x == 0) {
       int steal = s_steal;
-      s_row = SPARSE ? next_work(ctr, wk, blockIdx.x & 7, steal) : next_row(ctr, wk.rows, blockIdx.x & 7, steal);
+      const QueuePtr a = queue_args();
+      s_row = SPARSE ? next_work(a, blockIdx.x & 7, steal) : next_row(a->ctr, a->rows, blockIdx.x & 7, steal);
       s_steal = steal;
     }
     __syncthreads();
@@ -1067,14 +1097,14 @@ __global__ __launch_bounds__(kThreads, OCC) void attn_bf16_kernel(
     if (w < 0) break;
     int4 un = make_int4(w, 0, NB, -1);
     if constexpr (SPARSE) {
-      un = work_at(wk, w);
+      un = work_at(queue_args(), w);
       if (un.x < 0) {
         __syncthreads();
         continue;
       }
     }
     bf16_row<D, SPARSE, PV, ENT, TOK>(un.x, un.y, un.z, un.w, smemK, smemV, smemKinfo, smemCols, q, ktile, vtile, o,
-                                      lse, entropy, perm, cols, N, n_pad, NB, scale_log2, tk, part, pstats);
+                                      lse, entropy, perm, cols, N, n_pad, NB, scale_log2, tk);
   }
 }
 
@@ -1115,7 +1145,7 @@ __device__ __forceinline__ void k64_row(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ ktile, const uint16_t* __restrict__ vtile,
     uint16_t* __restrict__ o, float* __restrict__ lse, const int32_t* __restrict__ perm,
     const int32_t* __restrict__ cols, const int32_t* __restrict__ bcount, int N, int n_pad, int NB,
-    float scale_log2, float* __restrict__ part, float* __restrict__ pstats) {
+    float scale_log2) {
   using G = Geo<D>;
   constexpr int KT_BYTES = kKT * D * 2;            // one 64-key tile of K or V^T
   constexpr int STEPS = KT_BYTES / 4096;           // 4 KB copy steps per tile
@@ -1309,7 +1339,7 @@ __device__ __forceinline__ void k64_row(
   const float lr_tot = sum_halves(st.lr);
   const float l_tot = LSE ? sum_halves(st.l) : 0.f;
   if (slot >= 0) {
-    write_partial<D>(oacc, st.m, lr_tot, l_tot, slot, wave * 32 + col, half, part, pstats);
+    write_partial<D>(oacc, st.m, lr_tot, l_tot, slot, wave * 32 + col, half);
     return;
   }
   if (!qvalid) return;
@@ -1338,26 +1368,23 @@ __device__ __forceinline__ void k64_row(
 // so that a call without them keeps its registers.
 template <int D, bool SPARSE, bool LSE, bool CUT = false>
 __global__ __launch_bounds__(kThreads, 3) void attn_k64_kernel(
-    const uint16_t* __restrict__ q, const uint16_t* __restrict__ ktile, const uint16_t* __restrict__ vtile,
+    QueueArgs, const uint16_t* __restrict__ q, const uint16_t* __restrict__ ktile, const uint16_t* __restrict__ vtile,
     uint16_t* __restrict__ o, float* __restrict__ lse, const int32_t* __restrict__ perm,
-    const int32_t* __restrict__ cnt, const int32_t* __restrict__ cols, const int32_t* __restrict__ order,
-    const int32_t* __restrict__ bcount, const int4* __restrict__ units, const int32_t* __restrict__ unit_hdr,
-    DenseSplit ds, int N, int n_pad, int NB, int rows, float scale_log2, int32_t* __restrict__ ctr, float* __restrict__ part,
-    float* __restrict__ pstats) {
-  const WorkArgs wk{cnt, order, units, unit_hdr, rows, NB};
+    const int32_t* __restrict__ cols, const int32_t* __restrict__ bcount, int N, int n_pad, int NB, float scale_log2) {
   constexpr int KT_BYTES = kKT * D * 2;
   __shared__ __attribute__((aligned(1024))) uint8_t smemK[KT_BYTES];
   __shared__ __attribute__((aligned(1024))) uint8_t smemV[KT_BYTES];
   extern __shared__ int32_t smemCols[];
   __shared__ int s_row, s_steal;  // thread 0's queue state lives in LDS, not in a register
   __shared__ int4 s_dense;
-  if (threadIdx.x == 0) s_steal = 0;
+  if (threadIdx.x == 0) s_steal = -1;
   for (;;) {
     if (threadIdx.x == 0) {
       int steal = s_steal;
-      if constexpr (SPARSE) s_row = next_work(ctr, wk, blockIdx.x & 7, steal);
-      else if constexpr (CUT) s_dense = next_dense(ctr, rows, NB, ds, blockIdx.x & 7, steal);
-      else s_row = next_row(ctr, rows, blockIdx.x & 7, steal);
+      const QueuePtr a = queue_args();
+      if constexpr (SPARSE) s_row = next_work(a, blockIdx.x & 7, steal);
+      else if constexpr (CUT) s_dense = next_dense(a, blockIdx.x & 7, steal);
+      else s_row = next_row(a->ctr, a->rows, blockIdx.x & 7, steal);
       s_steal = steal;
     }
     __syncthreads();
@@ -1366,21 +1393,21 @@ __global__ __launch_bounds__(kThreads, 3) void attn_k64_kernel(
       if (r < 0) break;
       k64_row<D, false, LSE>(r, __builtin_amdgcn_readfirstlane(s_dense.y), __builtin_amdgcn_readfirstlane(s_dense.z),
                              __builtin_amdgcn_readfirstlane(s_dense.w), smemK, smemV, smemCols, q, ktile, vtile, o,
-                             lse, perm, cols, bcount, N, n_pad, NB, scale_log2, part, pstats);
+                             lse, perm, cols, bcount, N, n_pad, NB, scale_log2);
     } else {
       const int w = s_row;
       if (w < 0) break;
       if constexpr (SPARSE) {
-        const int4 un = work_at(wk, __builtin_amdgcn_readfirstlane(w));
+        const int4 un = work_at(queue_args(), __builtin_amdgcn_readfirstlane(w));
         if (un.x < 0) {
           __syncthreads();
           continue;
         }
         k64_row<D, true, LSE>(un.x, un.y, un.z, un.w, smemK, smemV, smemCols, q, ktile, vtile, o, lse, perm, cols,
-                              bcount, N, n_pad, NB, scale_log2, part, pstats);
+                              bcount, N, n_pad, NB, scale_log2);
       } else {
         k64_row<D, false, LSE>(w, 0, NB, -1, smemK, smemV, smemCols, q, ktile, vtile, o, lse, perm, cols, bcount, N,
-                               n_pad, NB, scale_log2, part, pstats);
+                               n_pad, NB, scale_log2);
       }
     }
   }
@@ -1967,9 +1994,10 @@ hipError_t launch_prep(const tra_plan_s& p, const AttnArgs& a, int grid, hipStre
   return hipGetLastError();
 }
 
-// The unit table of a call, NULL where its rows are its work.
-const int4* unit_table(const tra_plan_s& p, const AttnArgs& a) {
-  return has_units(p, a) ? (const int4*)p.d_units : nullptr;
+// The queue of a call's attention kernel; no unit table where its rows are its work.
+QueueArgs make_queue(const tra_plan_s& p, const AttnArgs& a, DenseSplit ds = {0, 1}) {
+  return {a.cnt, a.order, has_units(p, a) ? (const int4*)p.d_units : nullptr, p.d_unit_hdr, p.d_row_ctr, p.d_part,
+          p.d_pstats, p.rows, p.NB, ds};
 }
 
 // The cut of a dense call for `cap` resident workgroups.  Its rows are equal, so a
@@ -2020,9 +2048,9 @@ hipError_t launch_k64_kernel(const tra_plan_s& p, const AttnArgs& a, int cap, De
   if (e != hipSuccess) return e;
   if (a.ev_start) (void)hipEventRecord(a.ev_start, s);
   hipLaunchKernelGGL((attn_k64_kernel<D, SPARSE, LSE, CUT>), dim3(grid), dim3(kThreads), lds_bytes, s,
-                     (const uint16_t*)a.q, p.d_kt, p.d_vt, (uint16_t*)a.o, a.lse, p.d_perm, a.cnt, a.cols, a.order,
-                     p.cfg.block_layout == TRA_BLOCKS_TILES ? p.d_bcount : nullptr, unit_table(p, a), p.d_unit_hdr, ds,
-                     p.S, p.n_pad, p.NB, p.rows, scale_log2, p.d_row_ctr, p.d_part, p.d_pstats);
+                     make_queue(p, a, ds), (const uint16_t*)a.q, p.d_kt, p.d_vt, (uint16_t*)a.o, a.lse, p.d_perm,
+                     a.cols, p.cfg.block_layout == TRA_BLOCKS_TILES ? p.d_bcount : nullptr, p.S, p.n_pad, p.NB,
+                     scale_log2);
   return attention_launched(a, s);
 }
 
@@ -2266,7 +2294,7 @@ __global__ __launch_bounds__(kFusedThreads, 1) void attn_fused_kernel(
   __shared__ __attribute__((aligned(1024))) uint8_t smem[4 * TILE];
   __shared__ float smemState[4 * kBQ];
   __shared__ int s_row, s_steal;
-  if (threadIdx.x == 0) s_steal = 0;
+  if (threadIdx.x == 0) s_steal = -1;
   for (;;) {
     if (threadIdx.x == 0) {
       int steal = s_steal;
@@ -2559,9 +2587,8 @@ hipError_t launch_variant(const tra_plan_s& p, const AttnArgs& a, hipStream_t s)
   if (e != hipSuccess) return e;
   if (a.ev_start) (void)hipEventRecord(a.ev_start, s);
   hipLaunchKernelGGL((attn_bf16_kernel<D, SPARSE, PV, ENT, 2, TOK>), dim3(grid), dim3(kThreads), lds_bytes, s,
-                     (const uint16_t*)a.q, p.d_kt, p.d_vt, (uint16_t*)a.o, a.lse, a.entropy, p.d_perm, a.cnt,
-                     a.cols, a.order, unit_table(p, a), p.d_unit_hdr, p.S, p.n_pad, p.NB, p.rows, scale_log2, tk,
-                     p.d_row_ctr, p.d_part, p.d_pstats);
+                     make_queue(p, a), (const uint16_t*)a.q, p.d_kt, p.d_vt, (uint16_t*)a.o, a.lse, a.entropy,
+                     p.d_perm, a.cols, p.S, p.n_pad, p.NB, scale_log2, tk);
   e = attention_launched(a, s);
   return e != hipSuccess || !has_units(p, a) ? e : launch_merge<D>(p, a, p.splits_cap, s);
 }

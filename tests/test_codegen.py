@@ -154,3 +154,12 @@ def test_key_splitting_kernel_registers(assembly):
         for kname, lines in _kernels(text):
             if "attn_small_kernel" in kname:
                 assert not [t for t in lines if t.startswith(("scratch_", "flat_"))], kname
+
+
+def test_attention_kernels_do_not_spill(assembly):
+    """No attention kernel of the bf16 path keeps a register, vector or scalar, in
+    scratch memory or in lanes of another register."""
+    kernels = {n: f for n, f in _metadata(assembly["attn_bf16.hip"]).items() if "attn_" in n}
+    assert len(kernels) >= 30
+    for name, f in kernels.items():
+        assert f["vgpr_spill_count"] == f["sgpr_spill_count"] == f["private_segment_fixed_size"] == 0, name
