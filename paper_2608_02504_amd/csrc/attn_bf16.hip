@@ -1550,40 +1550,54 @@ __device__ void plan_units(const PlanArgs& a, uint8_t* lds) {
     for (int w = 0; w < kPrepWaves; ++w) x += ((const long long*)s_wave)[w];
     return x;
   };
-  auto block_max = [&](int x) {
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) x = max(x, __shfl_xor(x, o));
-    __syncthreads();
-    if (lane == 0) s_wave[wave] = x;
-    __syncthreads();
-#pragma unroll
-    for (int w = 0; w < kPrepWaves; ++w) x = max(x, s_wave[w]);
-    return x;
-  };
   long long tot = 0;
   for (int k = k0; k < k1; ++k) tot += max(len_of(row_at(k)), 0);
   const long long total = block_sum(tot);
   const long long share = (long long)max(a.n_wg, 1) * kSplitPerWG;
   int L = (int)max((long long)kSplitMin, (total + share - 1) / share);
   {
-    // pieces and longest unit under each candidate length, then the cheapest
-    const int L0 = L;
-    long long best = LLONG_MAX;
-#pragma unroll 1  // (unrolled, its counters push the whole pre-pass past 64 registers)
-    for (int i = 0; i < kSplitCands; ++i) {
-      const int Lc = split_cand(L0, i);
+    // pieces and longest unit under each candidate length, three waves a candidate,
+    // then the cheapest.  (One candidate after another, each a walk and two block-wide
+    // reductions, made the pre-pass of 118 rows 18 us, now 11, and cost 1.5 % of a call
+    // of 35,460 rows at head_dim 64, whose lengths are read from memory.)
+    constexpr int CW = kPrepWaves / kSplitCands, CT = 64 * CW;
+    int* s_cand = s_tail;  // [wave] pieces, longest (the buckets are not in use yet)
+    const int i = wave / CW;
+    if (i < kSplitCands) {
+      const int Lc = split_cand(L, i);
       int n = 0, longest = 0;
-#pragma unroll 1
-      for (int k = k0; k < k1; ++k) {
+#pragma unroll 4
+      for (int k = t - i * CT; k < rows; k += CT) {
         const int c = len_of(row_at(k));
         const int pieces = c > Lc ? (c + Lc - 1) / Lc : 1;
         n += pieces > 1 ? pieces : 0;
         longest = max(longest, pieces > 1 ? (c + pieces - 1) / pieces : c);
       }
-      const long long cost = block_sum(n) * (4 * kPieceCost) + (long long)a.n_wg * block_max(longest);
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        n += __shfl_xor(n, o);
+        longest = max(longest, __shfl_xor(longest, o));
+      }
+      if (lane == 0) {
+        s_cand[2 * wave] = n;
+        s_cand[2 * wave + 1] = longest;
+      }
+    }
+    __syncthreads();
+    const int L0 = L;
+    long long best = LLONG_MAX;
+#pragma unroll 1
+    for (int c = 0; c < kSplitCands; ++c) {
+      long long n = 0;
+      int longest = 0;
+      for (int w = 0; w < CW; ++w) {
+        n += s_cand[2 * (c * CW + w)];
+        longest = max(longest, s_cand[2 * (c * CW + w) + 1]);
+      }
+      const long long cost = n * (4 * kPieceCost) + (long long)a.n_wg * longest;
       if (cost < best) {
         best = cost;
-        L = Lc;
+        L = split_cand(L0, c);
       }
     }
   }
