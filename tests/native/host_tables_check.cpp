@@ -106,6 +106,13 @@ int main() {
       }
     }
     expect(video == N && text == c.text_tokens, "block token counts", ic);
+    if (c.dtype == TRA_FP32) {  // the block mask's key vectors alone, not the bf16 kernels' key words
+      tra::HostTables k;
+      tra::build_host_tables(c, &k, false, false, false, false, true);
+      expect(k.kinfo.empty(), "key words of an fp32 plan", ic);
+      expect(k.kfeat.size() == (c.distance == TRA_DIST_2D ? (size_t)t.NB * c.block * tra::kKeyFeat : 0),
+             "key-feature table of an fp32 plan", ic);
+    }
     if (c.dtype == TRA_BF16) {
       expect(t.kinfo.size() == (size_t)(t.NB + 1) * tra::kKeyInfo, "key-word table size", ic);
       for (int p = 0; p < S; ++p) {
