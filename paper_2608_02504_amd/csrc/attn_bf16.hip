@@ -332,8 +332,7 @@ __device__ __forceinline__ float tile_max(const f32x16 (&s)[4], float scale_log2
 // With PV the rounded pairs are also added to the four accumulation chains
 // lr4, which a caller carries over all sub-tiles of a tile (one long chain of
 // dot products would stall the wave on their latency); with LF the fp32
-// weights into lsum.  tile_exp: the same for one sub-tile, with its own
-// chains, their total added to lrsum.
+// weights into lsum.
 template <bool PV, bool ENT, bool LF = true>
 __device__ __forceinline__ void tile_exp_acc(const f32x16& s, float scale_log2, float m, float& lsum,
                                              float& asum, float (&lr4)[4], uint32_t* pb) {
@@ -350,14 +349,6 @@ __device__ __forceinline__ void tile_exp_acc(const f32x16& s, float scale_log2, 
       lr4[(e >> 1) & 3] = add_bf16_pair(pb[e >> 1], lr4[(e >> 1) & 3]);
     }
   }
-}
-
-template <bool PV, bool ENT, bool LF = true>
-__device__ __forceinline__ void tile_exp(const f32x16& s, float scale_log2, float m, float& lsum,
-                                         float& asum, float& lrsum, uint32_t* pb) {
-  float lr4[4] = {0.f, 0.f, 0.f, 0.f};
-  tile_exp_acc<PV, ENT, LF>(s, scale_log2, m, lsum, asum, lr4, pb);
-  if (PV) lrsum += (lr4[0] + lr4[1]) + (lr4[2] + lr4[3]);
 }
 
 // O^T += V^T P^T.  k-step ks covers keys [16ks, 16ks+16); in lane half h the
