@@ -1,7 +1,7 @@
-"""Replays of captured HIP graphs of the attention calls.  The persistent
-attention kernels reset their row-queue counters with a small kernel (not a
-memset), so a captured launch sequence must give the eager result on every
-replay.  Each graph is replayed several times with the program's own eager
+"""Replays of captured HIP graphs of the attention calls.  The pre-pass resets the
+row-queue counters of the persistent kernels (the token-level one here; the others:
+test_gpu_many_rows.py) with plain stores, not a memset, so a captured launch
+sequence must give the eager result on every replay.  Each graph is replayed several times with the program's own eager
 work and synchronisations in between, and every replay is compared bit for
 bit with the eager call."""
 import numpy as np

@@ -51,8 +51,8 @@ SMALL = {
     # a single frame: only the frame distance 0 exists
     "one_frame_bf16": synth.Workload("one_frame_bf16", 1, 2, 128, "bf16", 1, 30, 52, 128,
                                      0.25, 4.0, 0.6, seed=86, tile_h=8, tile_w=16),
-    # 61 blocks per head and a small total: block-sparse rows longer than 48
-    # blocks are computed in merged pieces
+    # 61 blocks per head, 122 rows: the key-splitting kernel's (the same grid with
+    # rows in merged pieces: test_gpu_many_rows.py, test_gpu_prepass.py)
     "split_bf16": synth.Workload("split_bf16", 1, 2, 128, "bf16", 5, 30, 52, 128,
                                  0.25, 4.0, 0.6, seed=88, tile_h=8, tile_w=16),
 }
@@ -278,10 +278,11 @@ def test_entropy_closed_forms(dtype):
 
 def test_scores_jumping_in_late_tiles():
     """Scores that rise block by block along the tile-major order (0, 5, 15,
-    35 nats plus a small spread): after the first tile the entropy and token
-    kernels take weights against the reference without a tile max, accept the
-    +5 nat tile (weights up to 2^7.2) and redo the +15 and +35 nat tiles from
-    their max (weights past 2^20).  Entropy-only, fused entropy + output,
+    35 nats plus a small spread): after the first tile the token kernel (and on
+    plans of more rows, test_gpu_many_rows.py, the entropy kernel) takes weights
+    against the reference without a tile max, accepts the +5 nat tile (weights
+    up to 2^7.2) and redoes the +15 and +35 nat tiles from their max (weights
+    past 2^20).  Entropy-only, fused entropy + output,
     dense and token-level (full radius, every block listed) results against
     the oracle (Eq. 2, Eq. 1)."""
     _gpu()
@@ -341,8 +342,8 @@ def _close_to_rounding(a, b):
 def test_full_radius_sparse_equals_dense_bitwise(name):
     """All radii FULL -> every block retained -> the sparse kernel walks the
     same key blocks in the same order as the dense one: bitwise equal while
-    no row is split (lists of at most 48 blocks never are); a split row
-    (split_bf16: 61 blocks) is merged from pieces and agrees to rounding."""
+    no row is split (lists of at most 48 blocks never are); the 61 blocks of
+    split_bf16 are held to rounding, which rows merged from pieces agree to."""
     _gpu()
     w = SMALL[name]
     run = Run(w, radius_override=2 ** 31 - 1)
@@ -387,8 +388,9 @@ def test_out_of_range_column_ids_are_skipped(name):
     """Key-block ids outside [0, NB) in a list are skipped: padding every list
     with -1 and NB entries (between and around the valid ids) leaves o and lse
     equal to the call with the clean list -- bitwise where no row is split
-    (48 blocks or fewer), else to rounding (the longer padded lists are cut
-    into different pieces)."""
+    (48 blocks or fewer), else to rounding (longer padded lists may be cut
+    into different pieces).  Plans of this size take the key-splitting kernel;
+    the work units' lists: test_gpu_many_rows.py."""
     _gpu()
     import torch
     import paper_2608_02504_amd as tra
@@ -449,8 +451,8 @@ def test_row_schedule_does_not_change_results(name):
     """Rows are independent: the schedule (per-XCD row queues without an
     order, the heaviest-first order, a random permutation, an order with
     out-of-range entries that are skipped) changes only which workgroup
-    computes a row, and each result is bitwise the same; repeated calls start
-    from freshly reset row queues."""
+    computes a row, and each result is bitwise the same, call after call (on row
+    queues, which these row counts do not take: test_gpu_many_rows.py)."""
     _gpu()
     import torch
     import paper_2608_02504_amd as tra
