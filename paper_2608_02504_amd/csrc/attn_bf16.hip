@@ -2063,11 +2063,13 @@ template <int D, bool SPARSE, bool LSE>
 hipError_t launch_k64_lse(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) {
   const size_t lds_bytes = SPARSE ? (size_t)p.NB * sizeof(int32_t) : 0;
   if constexpr (!SPARSE) {
-    const int cap = resident_grid(attn_k64_kernel<D, false, LSE, true>, 0, p, INT_MAX);
-    const DenseSplit ds = dense_split(p.rows, p.NB, cap);
-    if (ds.tail > 0 && 8 * ds.tail * ds.pieces <= p.dense_slots) {  // (always within the plan's bound)
-      const hipError_t e = launch_k64_kernel<D, false, LSE, true>(p, a, cap, ds, s);
-      return e != hipSuccess ? e : launch_merge<D>(p, a, 8LL * ds.tail, s);
+    if (p.dense_slots > 0) {
+      const int cap = resident_grid(attn_k64_kernel<D, false, LSE, true>, 0, p, INT_MAX);
+      const DenseSplit ds = dense_split(p.rows, p.NB, cap);
+      if (ds.tail > 0 && 8 * ds.tail * ds.pieces <= p.dense_slots) {  // (always within the plan's bound)
+        const hipError_t e = launch_k64_kernel<D, false, LSE, true>(p, a, cap, ds, s);
+        return e != hipSuccess ? e : launch_merge<D>(p, a, 8LL * ds.tail, s);
+      }
     }
   }
   const int cap = std::min(resident_grid(attn_k64_kernel<D, SPARSE, LSE>, lds_bytes, p, INT_MAX),
@@ -2619,6 +2621,7 @@ hipError_t launch_bf16_d(const tra_plan_s& p, const AttnArgs& a, hipStream_t s) 
 
 void dense_capacities(const tra_plan_s& p, int* splits, int* slots) {
   *splits = *slots = 0;
+  if (p.NBa < 2 * kSplitMin) return;  // too few blocks to cut a row
   const auto take = [&](auto kernel) {
     const DenseSplit ds = dense_split(p.rowsa, p.NBa, resident_grid(kernel, 0, p, INT_MAX));
     *splits = std::max(*splits, 8 * ds.tail);

@@ -68,8 +68,7 @@ uint16_t f16_bits_of_int(int v) {
   if (v == 0) return 0;
   const uint16_t sign = v < 0 ? 0x8000 : 0;
   unsigned a = (unsigned)(v < 0 ? -v : v);  // 1 .. 2048
-  int e = 0;
-  while ((a >> (e + 1)) != 0) ++e;           // a = 1.m x 2^e, e <= 11
+  const int e = 31 - __builtin_clz(a);       // a = 1.m x 2^e, e <= 11
   const unsigned mant = ((a << 10) >> e) & 0x3FF;
   return (uint16_t)(sign | ((unsigned)(e + 15) << 10) | mant);
 }
@@ -232,8 +231,8 @@ void build_host_tables(const tra_config& c, HostTables* t, bool with_perm_coord,
         const int i = p < t->P ? perm[p] : -1;
         int v[kKeyFeat] = {0, 0, 0, 0, 0, 0, 0, 0};
         if (i >= 0 && i < t->N) {
-          const int x = (i / W) % H, y = i % W, sq = x * x + y * y;
-          const int o = i / (H * W) != f0 ? 2 : 0;
+          const int f = i / (H * W), r = i - f * H * W, x = r / W, y = r - x * W, sq = x * x + y * y;
+          const int o = f != f0 ? 2 : 0;
           v[o] = 2048;
           v[o + 1] = 1;
           v[4] = -(sq >> 11);
