@@ -255,7 +255,7 @@ tra_status tra_entropy(tra_plan plan, const void* q, const void* k, const void* 
                        void* stream);
 
 /* Entropy -> budget -> squared radius, per token (Sec. 3.1-3.2; App. C.1,
- * Eq. implementation-budget-radius: a bisection over the plan's count table).
+ * Eq. implementation-budget-radius: an indexed search of the plan's count table).
  * For a video token, K_hat is evaluated in fp64 by the plan's mapping and
  * clamped to [1, S]:
  *   UNIFORM    K_hat = ceil(tau * exp(H));

@@ -41,7 +41,7 @@ SMALL = {
     "fp32_b64_d128": synth.Workload("fp32_b64_d128", 1, 1, 128, "fp32", 2, 9, 11, 64,
                                     0.25, 4.0, 0.6, seed=82, tile_h=8, tile_w=8),
     # 45-token frames: each 128-token block spans three or four frames, which the
-    # mask builder's two-frame packed pair test does not cover
+    # mask builder's pair test on the matrix cores (two frames) does not cover
     "small_frames_bf16": synth.Workload("small_frames_bf16", 1, 2, 64, "bf16", 7, 5, 9, 128,
                                         0.25, 4.0, 0.6, seed=83, tile_h=8, tile_w=16),
     # the largest frame count a plan accepts (64): per-query thresholds for 64
@@ -57,8 +57,7 @@ SMALL = {
                                  0.25, 4.0, 0.6, seed=88, tile_h=8, tile_w=16),
 }
 
-# 90 x 160 frames: n_cap = 89^2 + 159^2 = 33,202, beyond the range of the mask
-# builder's 16-bit packed distances, so every pair takes the 32-bit test.
+# 90 x 160 frames: n_cap = 89^2 + 159^2 = 33,202, squared distances beyond 16 bits.
 WIDE = synth.Workload("wide_frame_bf16", 1, 1, 64, "bf16", 2, 90, 160, 128,
                       0.25, 4.0, 0.6, seed=84, tile_h=8, tile_w=16)
 
@@ -188,7 +187,7 @@ def test_mid_radius_masks_exact(name, radius, rule, distance):
 @pytest.mark.parametrize("budget", [1500, 6000])
 def test_wide_frame_sampled(budget):
     """Every stage on sampled query blocks of the 90 x 160 grid, with one constant
-    entropy ln(budget / tau) for every token: the radius bisection runs over
+    entropy ln(budget / tau) for every token: the radius search runs over
     [0, 33,202] and the block masks are partial."""
     _gpu()
     w = WIDE
