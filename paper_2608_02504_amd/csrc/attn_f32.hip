@@ -23,7 +23,7 @@
 // which keeps the wave inside 256 registers.
 //
 // Measured (MI355X), against one thread per query and scalar FMAs: entropy with
-// output at 4 heads x 3,510 tokens x 128, 13.69 -> 0.279 ms (1.8 -> 91 TFLOP/s; a
+// output at 4 heads x 3,510 tokens x 128, 13.69 -> 0.276 ms (1.8 -> 91 TFLOP/s; a
 // large fp32 GEMM reaches 155 here, and 440 workgroups on 256 CUs are two rounds
 // of one, which bounds it at 0.19); the whole chain on 256 tokens x 2 heads x 64,
 // 1,018 -> 41 us.  Error against fp64: 4.5e-6 -> 1.6e-6 (2-norm, relative).

@@ -18,13 +18,14 @@
 // lines it touches: a bisection over 8,178 entries touches about nine (3.3 GB for
 // 3.0 million queries, which took 0.44 ms).  Each row therefore has a small index,
 // the counts that end every 32 entries (level B) and every 512 (level A).  A query
-// takes the 64-byte run of A that holds K_hat (by bisection where A has several: n_cap
-// >= 8,192), then one run of B and one 128-byte line of the row, counting in each the
-// entries below K_hat, B and the line by independent 16-byte loads.  Workgroups walk
-// the heads of one run of tokens in turn, so that those on one XCD share A and B
-// in its L2.  75,600 tokens x 40 heads: 443 -> 96 us.  A's runs read one after another
-// instead: 9.8 us against 5.6 at 1 x 512 x 2 x 64 heads (n_cap 261,122, 32 runs), 5.8
-// against 6.4 at 1 x 128 x 128 x 8 heads (4 runs).
+// takes the 64-byte run of A that holds K_hat (the first, or the one found by bisection
+// of the others where A has several: n_cap >= 8,192), then one run of B and one 128-byte
+// line of the row, counting in each the entries below K_hat, B and the line by
+// independent 16-byte loads.  Workgroups walk the heads of one run of tokens in turn, so
+// that those on one XCD share A and B in its L2.  75,600 tokens x 40 heads: 443 -> 96 us.
+// A's runs read one after another instead: 9.8 us against 5.3 at 1 x 512 x 2 x 64 heads
+// (n_cap 261,122, 32 runs), 5.7 both ways at 2 x 90 x 160 x 4 heads (5 runs, most radii
+// in the first).
 // Plans whose table would exceed a size limit keep only C(n_cap) per position and
 // count the other radii on the fly (exact lattice counts, row by row), by
 // bisection.  Counts are exact integers either way.
@@ -202,18 +203,25 @@ __global__ __launch_bounds__(256) void budget_radius_kernel(
     const int fq = min(f, F - 1 - f), xq = min(x, H - 1 - x), yq = min(y, W - 1 - y);
     const size_t p = (size_t)(fq * hh + xq) * wh + yq;
     const int32_t* A = cidx + p * L.index();
-    int run = 0;  // the first run of A whose end reaches khat (the last one may not)
-    for (int n = (L.na + kRun - 1) / kRun; n > 1;) {
-      const int h = n / 2;
-      const bool past = A[(run + h) * kRun - 1] < khat;
-      run += past ? h : 0;
-      n = past ? n - h : h;
-    }
-    int g = run * kRun;
-    for (int a = g; a < min(L.na, run * kRun + kRun); a += 4) {
-      const int c = count_below<1>(A + a, khat);
-      g += c;
-      if (c < 4) break;
+    auto scan = [&](int run) {  // entries of A below khat, if its first `run` runs all are
+      int g = run * kRun;
+      for (int a = g; a < min(L.na, run * kRun + kRun); a += 4) {
+        const int c = count_below<1>(A + a, khat);
+        g += c;
+        if (c < 4) break;
+      }
+      return g;
+    };
+    int g = scan(0);
+    if (g == kRun && L.na > kRun) {
+      int run = 1;  // the first run whose end reaches khat (the last one may not)
+      for (int n = (L.na + kRun - 1) / kRun - 1; n > 1;) {
+        const int h = n / 2;
+        const bool past = A[(run + h) * kRun - 1] < khat;
+        run += past ? h : 0;
+        n = past ? n - h : h;
+      }
+      g = scan(run);
     }
     if (g == L.na) {
       n = TRA_RADIUS_FULL;  // (A ends with C(n_cap))
